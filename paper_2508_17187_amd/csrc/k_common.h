@@ -245,11 +245,6 @@ __device__ __forceinline__ double wave_sum(double v) {
     for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
     return v;
 }
-__device__ __forceinline__ long long wave_sum_ll(long long v) {
-    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
-    return v;
-}
-
 
 // Exact t / S and t % S for 0 <= t < 2^22 through a float reciprocal.
 __device__ __forceinline__ void divmod_small(int t, int S, float invS, int &q, int &r) {

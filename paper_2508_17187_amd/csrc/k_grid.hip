@@ -42,6 +42,81 @@ hipError_t launch_zero(void *p, size_t bytes, hipStream_t s) {
 }
 
 // ---------------------------------------------------------------------------
+// Totals of a presum workgroup: the class counts of its threads, and their
+// sums of weights per pol, added to the outputs.  Every workgroup adds to
+// the same few words, and the L2 takes such requests one after another
+// (about 6 ns each): one request per wavefront and word made 160 us of the
+// 208 us presum of 13.5 M visibilities.  So the wavefronts' totals meet in
+// LDS first, and the words of one output go out as one request (lane p adds
+// word p): two requests per workgroup, 14 times fewer.
+// plane: the output plane of the thread's samples (-1: none kept).  Threads
+// of one wavefront with different planes (cube channels) add their own sums;
+// ROWS threads cl, cl + 64 / ROWS, ... of a wavefront share a plane and are
+// summed first.  Every thread of the workgroup must call it.
+template <int NPOL, int ROWS>
+__device__ __forceinline__ void add_totals(int kept, int flagged, int dropped, double (&sw)[NPOL],
+                                           int plane, double *sumwt, long long *counters) {
+    __shared__ int cnt[4][3];
+    __shared__ double sums[4][NPOL];
+    __shared__ int planes[4];
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    if (counters) {
+        for (int off = 32; off > 0; off >>= 1) {
+            kept += __shfl_xor(kept, off);
+            flagged += __shfl_xor(flagged, off);
+            dropped += __shfl_xor(dropped, off);
+        }
+        if (lane == 0) {
+            cnt[wv][0] = kept;
+            cnt[wv][1] = flagged;
+            cnt[wv][2] = dropped;
+        }
+    }
+    if (sumwt) {
+        const unsigned long long has = __ballot(plane >= 0);
+        const int lead = has ? __shfl(plane, __ffsll((long long)has) - 1) : -1;
+        const bool uniform = __all(plane < 0 || plane == lead);
+        for (int off = 32; off >= 64 / ROWS && off > 0; off >>= 1) {
+            for (int p = 0; p < NPOL; ++p) sw[p] += __shfl_xor(sw[p], off);
+            plane = max(plane, __shfl_xor(plane, off));
+        }
+        if (uniform) {
+            for (int off = 32 / ROWS; off > 0; off >>= 1)
+                for (int p = 0; p < NPOL; ++p) sw[p] += __shfl_xor(sw[p], off);
+        } else if (plane >= 0 && lane < 64 / ROWS) {
+            for (int p = 0; p < NPOL; ++p)
+                if (sw[p] != 0.0) atomicAdd(&sumwt[plane * NPOL + p], sw[p]);
+        }
+        if (lane == 0) {
+            planes[wv] = uniform ? lead : -1;
+            for (int p = 0; p < NPOL; ++p) sums[wv][p] = sw[p];
+        }
+    }
+    __syncthreads();
+    if (wv != 0) return;
+    if (counters && lane < 3) {
+        long long c = 0;
+        for (int w = 0; w < 4; ++w) c += cnt[w][lane];
+        if (c) atomicAdd((unsigned long long *)&counters[lane], (unsigned long long)c);
+    }
+    if (sumwt && lane < NPOL) {
+        // wavefronts of one plane add up; a change of plane flushes
+        double s = 0.0;
+        int at = -1;
+        for (int w = 0; w < 4; ++w) {
+            if (planes[w] < 0) continue;
+            if (planes[w] != at) {
+                if (at >= 0 && s != 0.0) atomicAdd(&sumwt[at * NPOL + lane], s);
+                at = planes[w];
+                s = 0.0;
+            }
+            s += sums[w][lane];
+        }
+        if (at >= 0 && s != 0.0) atomicAdd(&sumwt[at * NPOL + lane], s);
+    }
+}
+
+// ---------------------------------------------------------------------------
 // presum + counters: one thread per sorted kept pair, a segmented scan over
 // the wavefront by group, one atomic per group segment of the wave (into A,
 // zeroed beforehand); threads past the kept pairs count the dropped and
@@ -53,7 +128,7 @@ __global__ __launch_bounds__(256) void k_presum(
     long long *counters) {
     const int lane = threadIdx.x & 63;
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    long long kept = 0, flagged = 0, dropped = 0;
+    int kept = 0, flagged = 0, dropped = 0;
     double sw[NPOL];
     cpx<T> a[NPOL];
     for (int p = 0; p < NPOL; ++p) {
@@ -113,31 +188,7 @@ __global__ __launch_bounds__(256) void k_presum(
                 if (!UNIT) atomicAdd(&A[(int64_t)g * NPOL + p].y, a[p].y);
             }
     }
-    if (counters) {
-        kept = wave_sum_ll(kept);
-        flagged = wave_sum_ll(flagged);
-        dropped = wave_sum_ll(dropped);
-        if (lane == 0) {
-            if (kept) atomicAdd((unsigned long long *)&counters[0], (unsigned long long)kept);
-            if (flagged) atomicAdd((unsigned long long *)&counters[1], (unsigned long long)flagged);
-            if (dropped) atomicAdd((unsigned long long *)&counters[2], (unsigned long long)dropped);
-        }
-    }
-    if (sumwt) {
-        // one atomic per wavefront when every lane with a sample shares its plane
-        unsigned long long has = __ballot(plane >= 0);
-        int lead = has ? __shfl(plane, __ffsll((long long)has) - 1) : -1;
-        bool uniform = __all(plane < 0 || plane == lead);
-        if (uniform) {
-            for (int p = 0; p < NPOL; ++p) {
-                double s = wave_sum(sw[p]);
-                if (lane == 0 && lead >= 0 && s != 0.0) atomicAdd(&sumwt[lead * NPOL + p], s);
-            }
-        } else if (plane >= 0) {
-            for (int p = 0; p < NPOL; ++p)
-                if (sw[p] != 0.0) atomicAdd(&sumwt[plane * NPOL + p], sw[p]);
-        }
-    }
+    add_totals<NPOL, 1>(kept, flagged, dropped, sw, plane, sumwt, counters);
 }
 
 // ---------------------------------------------------------------------------
@@ -171,7 +222,7 @@ __global__ __launch_bounds__(256) void k_presum_col(
     // lanes of my column, and of my column before me, in a ballot
     const uint64_t colmask = 0x0101010101010101ull << cl;
     const uint64_t below = colmask & ((1ull << lane) - 1);
-    long long kept = 0, flagged = 0, dropped = 0;
+    int kept = 0, flagged = 0, dropped = 0;
     double sw[NPOL];
     cpx<T> carry[NPOL];
     for (int p = 0; p < NPOL; ++p) {
@@ -302,30 +353,7 @@ __global__ __launch_bounds__(256) void k_presum_col(
     }
     // the run still open may continue in the next wavefront
     if (SUMS && tl == 0 && carry_g >= 0) emit(carry_g, carry_alone, carry);
-    if (counters) {
-        kept = wave_sum_ll(kept);
-        flagged = wave_sum_ll(flagged);
-        dropped = wave_sum_ll(dropped);
-        if (lane == 0) {
-            if (kept) atomicAdd((unsigned long long *)&counters[0], (unsigned long long)kept);
-            if (flagged) atomicAdd((unsigned long long *)&counters[1], (unsigned long long)flagged);
-            if (dropped) atomicAdd((unsigned long long *)&counters[2], (unsigned long long)dropped);
-        }
-    }
-    if (sumwt) {
-        unsigned long long has = __ballot(plane >= 0);
-        int lead = has ? __shfl(plane, __ffsll((long long)has) - 1) : -1;
-        bool uniform = __all(plane < 0 || plane == lead);
-        if (uniform) {
-            for (int p = 0; p < NPOL; ++p) {
-                double s = wave_sum(sw[p]);
-                if (lane == 0 && lead >= 0 && s != 0.0) atomicAdd(&sumwt[lead * NPOL + p], s);
-            }
-        } else if (plane >= 0) {
-            for (int p = 0; p < NPOL; ++p)
-                if (sw[p] != 0.0) atomicAdd(&sumwt[plane * NPOL + p], sw[p]);
-        }
-    }
+    add_totals<NPOL, kColT>(kept, flagged, dropped, sw, plane, sumwt, counters);
 }
 
 // Work shape of the track presum: ncb column blocks x ceil(M / 64) step
