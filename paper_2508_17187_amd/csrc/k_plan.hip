@@ -94,57 +94,86 @@ hipError_t launch_debug_map(int64_t nrow, int32_t nchan, const double *uvw,
 // ---------------------------------------------------------------------------
 // Sort keys.  Fields from most to least significant: plane, A-term group,
 // w-plane, conj, p_v, p_u, [baseline, channel when a pointing phasor is
-// applied], o_v, o_u.  Keys of dropped or skipped pairs are all ones.
+// applied], o_v, o_u.  Keys of dropped or skipped pairs are all ones, which
+// no kept pair's 63 bits reach.
+constexpr uint64_t kDropKey = ~0ull;
+
 __device__ __forceinline__ void put(unsigned __int128 &key, uint32_t v, int bits) {
     if (bits) key = (key << bits) | (unsigned __int128)v;
 }
 
-__global__ void k_plan_keys(int64_t nrow, int32_t nchan, const double *uvw,
-                            const ChanConst *cc, MapGeom g, KeyLayout kl,
-                            const int32_t *ant1, const int32_t *ant2, int32_t nant,
-                            uint64_t *keys, int32_t *vals, unsigned long long *n_kept) {
-    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    bool kept = false;
-    if (i < nrow * nchan) {
-        int64_t r = i / nchan;
-        int32_t c = (int32_t)(i - r * nchan);
-        ChanConst ch = cc[c];
-        uint64_t key = ~0ull;
-        int32_t val = (int32_t)i;
-        if (ch.plane < 0) {
-            val |= (1 << 30);
-        } else {
-            Map m = map_sample(uvw[3 * r], uvw[3 * r + 1], uvw[3 * r + 2], ch, g);
-            if (m.keep) {
-                unsigned __int128 k128 = 0;
-                put(k128, (uint32_t)ch.plane, kl.b_plane);
-                put(k128, (uint32_t)ch.fg, kl.b_fg);
-                put(k128, (uint32_t)m.k, kl.b_k);
-                put(k128, (uint32_t)m.conj, kl.b_conj);
-                put(k128, (uint32_t)m.pv, kl.b_pv);
-                put(k128, (uint32_t)m.pu, kl.b_pu);
-                if (kl.b_bl) put(k128, (uint32_t)(ant1[r] * nant + ant2[r]), kl.b_bl);
-                if (kl.b_ch) put(k128, (uint32_t)c, kl.b_ch);
-                put(k128, (uint32_t)(m.ov + (g.O >> 1)), kl.b_o);
-                put(k128, (uint32_t)(m.ou + (g.O >> 1)), kl.b_o);
-                key = (uint64_t)(k128 >> kl.shift);
-                kept = true;
-            }
+__global__ __launch_bounds__(256) void k_plan_keys(uint32_t n_pairs, uint32_t nchan,
+                                                   const double *uvw, const ChanConst *cc,
+                                                   MapGeom g, KeyLayout kl, const int32_t *ant1,
+                                                   const int32_t *ant2, int32_t nant,
+                                                   uint64_t *keys, int32_t *vals) {
+    const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= n_pairs) return;
+    const uint32_t r = i / nchan, c = i - r * nchan;
+    const ChanConst ch = cc[c];
+    uint64_t key = kDropKey;
+    int32_t val = (int32_t)i;
+    if (ch.plane < 0) {
+        val |= (1 << 30);
+    } else {
+        const double *q = uvw + 3 * (int64_t)r;
+        Map m = map_sample(q[0], q[1], q[2], ch, g);
+        if (m.keep) {
+            unsigned __int128 k128 = 0;
+            put(k128, (uint32_t)ch.plane, kl.b_plane);
+            put(k128, (uint32_t)ch.fg, kl.b_fg);
+            put(k128, (uint32_t)m.k, kl.b_k);
+            put(k128, (uint32_t)m.conj, kl.b_conj);
+            put(k128, (uint32_t)m.pv, kl.b_pv);
+            put(k128, (uint32_t)m.pu, kl.b_pu);
+            if (kl.b_bl) put(k128, (uint32_t)(ant1[r] * nant + ant2[r]), kl.b_bl);
+            if (kl.b_ch) put(k128, c, kl.b_ch);
+            put(k128, (uint32_t)(m.ov + (g.O >> 1)), kl.b_o);
+            put(k128, (uint32_t)(m.ou + (g.O >> 1)), kl.b_o);
+            key = (uint64_t)(k128 >> kl.shift);
         }
-        keys[i] = key;
-        vals[i] = val;
     }
-    // one atomic per wavefront
-    unsigned long long b = __ballot(kept);
-    if ((threadIdx.x & 63) == 0 && b) atomicAdd(n_kept, (unsigned long long)__popcll(b));
+    keys[i] = key;
+    vals[i] = val;
 }
 
-__global__ void k_group_flags(const uint64_t *keys, int64_t n_kept, int32_t merged,
-                              int32_t *flags) {
-    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n_kept) return;
-    flags[i] = (!merged || i == 0 || keys[i] != keys[i - 1]) ? 1 : 0;
+// Tiles [tx0, tx1] x [ty0, ty1] a footprint overlaps.
+__device__ __forceinline__ void tile_span(int pu, int pv, int h, int &tx0, int &tx1, int &ty0,
+                                          int &ty1) {
+    tx0 = (pu - h) / kTile;
+    tx1 = (pu + h) / kTile;
+    ty0 = (pv - h) / kTile;
+    ty1 = (pv + h) / kTile;
 }
+
+// What sorted pair i adds to the running totals: a group in the low word
+// and the tiles of its footprint in the high word when the pair begins a
+// group (its key differs from the one before it, or every pair is a group
+// of its own), else nothing.  The pixel and the w-plane come from the key
+// itself (the fields the shift may drop lie below them), so one scan over
+// the sorted keys numbers the groups and places their tile pairs.
+struct GroupHead {
+    const uint64_t *keys;
+    const int32_t *h;
+    KeyLayout kl;
+    int32_t merged;
+    __device__ uint64_t operator()(uint32_t i) const {
+        const uint64_t key = keys[i];
+        if (key == kDropKey || (merged && i > 0 && keys[i - 1] == key)) return 0;
+        uint64_t f = key >> (2 * kl.b_o + kl.b_ch + kl.b_bl - kl.shift);
+        auto field = [&](int bits) {
+            const int v = (int)(f & ((1ull << bits) - 1));
+            f >>= bits;
+            return v;
+        };
+        const int pu = field(kl.b_pu), pv = field(kl.b_pv);
+        f >>= kl.b_conj;
+        const int k = field(kl.b_k);
+        int tx0, tx1, ty0, ty1;
+        tile_span(pu, pv, h[k], tx0, tx1, ty0, ty1);
+        return 1ull | ((uint64_t)((tx1 - tx0 + 1) * (ty1 - ty0 + 1)) << 32);
+    }
+};
 
 __device__ __forceinline__ double airy_power(double x) {
     if (x == 0.0) return 1.0;
@@ -152,218 +181,210 @@ __device__ __forceinline__ double airy_power(double x) {
     return b * b;
 }
 
-__global__ void k_group_meta(const int32_t *vals, const int32_t *flags, const int32_t *gidx,
-                             int64_t n_kept, int32_t nchan, const double *uvw,
-                             const ChanConst *cc, MapGeom g, CFView cf,
-                             const int32_t *ant1, const int32_t *ant2,
-                             const double *ant_dlm, double du_dl, double dv_dm,
-                             int32_t *group_start, GroupMeta *groups, int64_t *geo) {
-    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n_kept || !flags[i]) return;
-    int32_t gi = gidx[i];
-    group_start[gi] = (int32_t)i;
-    int32_t pair = vals[i] & ~(1 << 30);
-    int64_t r = pair / nchan;
-    int32_t c = pair - (int32_t)r * nchan;
-    ChanConst ch = cc[c];
-    Map m = map_sample(uvw[3 * r], uvw[3 * r + 1], uvw[3 * r + 2], ch, g);
-    GroupMeta gm;
-    int32_t h = g.h[m.k];
-    int64_t S = 2 * h + 1;
-    int64_t no = g.O + 1;
-    gm.cf_off = cf.plane_off[(int64_t)ch.fg * g.n_w + m.k] +
-                ((int64_t)(m.ov + (g.O >> 1)) * no + (m.ou + (g.O >> 1))) * S * S;
-    gm.cell = ((int64_t)ch.plane * g.npol) * (int64_t)g.ny * g.nx + (int64_t)m.pv * g.nx + m.pu;
-    gm.pu = m.pu;
-    gm.pv = m.pv;
-    gm.k = m.k;
-    gm.conj = m.conj;
-    gm.ou = m.ou;
-    gm.ov = m.ov;
-    gm.plane = ch.plane;
-    gm.fg = ch.fg;
-    gm.h = h;
-    gm.sc = cf.scale[(int64_t)ch.fg * g.n_w + m.k];
-    gm.f = 1.0;
-    gm.bu = 0.0;
-    gm.bv = 0.0;
-    if (ant1) {
-        int32_t a1 = ant1[r], a2 = ant2[r];
-        double l1 = ant_dlm[2 * a1], m1 = ant_dlm[2 * a1 + 1];
-        double l2 = ant_dlm[2 * a2], m2 = ant_dlm[2 * a2 + 1];
-        double dl = 0.5 * (l1 + l2), dm = 0.5 * (m1 + m2);
-        double ddl = l1 - l2, ddm = m1 - m2;
-        double dist = sqrt(ddl * ddl + ddm * ddm);
-        gm.f = airy_power(ch.fscale * 0.5 * dist);
-        gm.bu = (du_dl * dl) / (double)g.O;
-        gm.bv = (dv_dm * dm) / (double)g.O;
+// Sums of a workgroup's threads added to *out, one request per workgroup.
+__device__ __forceinline__ void block_add(unsigned long long v, unsigned long long *out) {
+    __shared__ unsigned long long part[4];
+    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
+    if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = v;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        v = part[0] + part[1] + part[2] + part[3];
+        if (v) atomicAdd(out, v);
     }
-    groups[gi] = gm;
-    geo[gi] = (int64_t)(uint16_t)m.pu | ((int64_t)(uint16_t)m.pv << 16) |
-              ((int64_t)(uint16_t)(int16_t)m.ou << 32) | ((int64_t)(uint16_t)(int16_t)m.ov << 48);
+    __syncthreads();
 }
 
-// The exclusive scan counts a group's own start for every later pair of the
-// group; turn it into the group index of every sorted position.
-__global__ void k_group_index(int32_t *gidx, const int32_t *flags, int64_t n_kept) {
-    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n_kept) gidx[i] += flags[i] - 1;
-}
+// Groups from the scan over the sorted pairs: the group of every pair, the
+// record of each group (written by its first pair) and its (tile, group)
+// pairs; the counts.  A bounded number of workgroups walks the pairs, so
+// that the totals cost a bounded number of atomic requests.
+constexpr int kMetaBlocks = 2048;
 
-__global__ void k_group_end(int32_t *group_start, int64_t n_groups, int64_t n_kept) {
-    if (threadIdx.x == 0) group_start[n_groups] = (int32_t)n_kept;
+__global__ __launch_bounds__(256) void k_group_meta(
+    const uint64_t *keys, const uint64_t *scan, const int32_t *vals, uint32_t n_pairs,
+    uint32_t nchan, const double *uvw, const ChanConst *cc, MapGeom g, CFView cf,
+    const int32_t *ant1, const int32_t *ant2, const double *ant_dlm, double du_dl, double dv_dm,
+    int32_t ntx, int32_t nty, int32_t *gidx, int32_t *group_start, GroupMeta *groups,
+    int64_t *geo, uint32_t *tile_keys, int32_t *tile_vals, PlanCounts *pc) {
+    unsigned long long taps = 0, tiles = 0;
+    for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < n_pairs;
+         i += gridDim.x * blockDim.x) {
+        if (keys[i] == kDropKey) continue;
+        const uint64_t now = scan[i], before = i > 0 ? scan[i - 1] : 0;
+        const int32_t gi = (int32_t)(uint32_t)now - 1;
+        gidx[i] = gi;
+        if (i + 1 == n_pairs || keys[i + 1] == kDropKey) {      // the last kept pair
+            group_start[gi + 1] = (int32_t)(i + 1);
+            pc->n_kept = (int32_t)(i + 1);
+            pc->n_groups = gi + 1;
+        }
+        if ((uint32_t)now == (uint32_t)before) continue;
+        group_start[gi] = (int32_t)i;
+        const uint32_t pair = (uint32_t)vals[i] & ~(1u << 30);
+        const uint32_t r = pair / nchan, c = pair - r * nchan;
+        const ChanConst ch = cc[c];
+        const double *q = uvw + 3 * (int64_t)r;
+        Map m = map_sample(q[0], q[1], q[2], ch, g);
+        GroupMeta gm;
+        const int32_t h = g.h[m.k];
+        const int64_t S = 2 * h + 1;
+        const int64_t no = g.O + 1;
+        gm.cf_off = cf.plane_off[(int64_t)ch.fg * g.n_w + m.k] +
+                    ((int64_t)(m.ov + (g.O >> 1)) * no + (m.ou + (g.O >> 1))) * S * S;
+        gm.cell = ((int64_t)ch.plane * g.npol) * (int64_t)g.ny * g.nx + (int64_t)m.pv * g.nx + m.pu;
+        gm.pu = m.pu;
+        gm.pv = m.pv;
+        gm.k = m.k;
+        gm.conj = m.conj;
+        gm.ou = m.ou;
+        gm.ov = m.ov;
+        gm.plane = ch.plane;
+        gm.fg = ch.fg;
+        gm.h = h;
+        gm.sc = cf.scale[(int64_t)ch.fg * g.n_w + m.k];
+        gm.f = 1.0;
+        gm.bu = 0.0;
+        gm.bv = 0.0;
+        if (ant1) {
+            int32_t a1 = ant1[r], a2 = ant2[r];
+            double l1 = ant_dlm[2 * a1], m1 = ant_dlm[2 * a1 + 1];
+            double l2 = ant_dlm[2 * a2], m2 = ant_dlm[2 * a2 + 1];
+            double dl = 0.5 * (l1 + l2), dm = 0.5 * (m1 + m2);
+            double ddl = l1 - l2, ddm = m1 - m2;
+            double dist = sqrt(ddl * ddl + ddm * ddm);
+            gm.f = airy_power(ch.fscale * 0.5 * dist);
+            gm.bu = (du_dl * dl) / (double)g.O;
+            gm.bv = (dv_dm * dm) / (double)g.O;
+        }
+        groups[gi] = gm;
+        geo[gi] = (int64_t)(uint16_t)m.pu | ((int64_t)(uint16_t)m.pv << 16) |
+                  ((int64_t)(uint16_t)(int16_t)m.ou << 32) |
+                  ((int64_t)(uint16_t)(int16_t)m.ov << 48);
+        taps += (unsigned long long)(S * S);
+        // the group's (tile, group) pairs
+        int tx0, tx1, ty0, ty1;
+        tile_span(m.pu, m.pv, h, tx0, tx1, ty0, ty1);
+        uint32_t o = (uint32_t)(before >> 32);
+        for (int ty = ty0; ty <= ty1; ++ty)
+            for (int tx = tx0; tx <= tx1; ++tx) {
+                tile_keys[o] = (uint32_t)(((int64_t)ch.plane * nty + ty) * ntx + tx);
+                tile_vals[o] = gi;
+                ++o;
+            }
+        tiles += (unsigned long long)((tx1 - tx0 + 1) * (ty1 - ty0 + 1));
+    }
+    block_add(taps, &pc->taps);
+    block_add(tiles, &pc->n_tile_pairs);
 }
 
 // ---- tiles of the gridder ----------------------------------------------------
-// Each group's footprint is cut by the 32 x 32 cell tiles it overlaps; the
-// (tile, group) pairs are sorted by tile and split into chunks of at most
-// `per` pairs, one workgroup each.
-__device__ __forceinline__ void tile_span(const GroupMeta &gm, int h, int &tx0, int &tx1,
-                                          int &ty0, int &ty1) {
-    tx0 = (gm.pu - h) / kTile;
-    tx1 = (gm.pu + h) / kTile;
-    ty0 = (gm.pv - h) / kTile;
-    ty1 = (gm.pv + h) / kTile;
-}
+// The (tile, group) pairs sorted by tile are cut into chunks of at most
+// `per` pairs, one workgroup each, and (separable tables) into the parts of
+// the separable gridder.  Everything follows from each tile's number of
+// pairs, so one scan over the tiles places them.
+struct TileSums {
+    uint32_t chunks;      // gridder chunks
+    uint32_t shared;      // tiles with several chunks
+};
 
-__global__ void k_tile_count(const GroupMeta *groups, int64_t n_groups, const int32_t *h,
-                             int32_t *counts) {
-    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n_groups) return;
-    GroupMeta gm = groups[i];
-    int tx0, tx1, ty0, ty1;
-    tile_span(gm, h[gm.k], tx0, tx1, ty0, ty1);
-    counts[i] = (tx1 - tx0 + 1) * (ty1 - ty0 + 1);
-}
+struct TileSumsPlus {
+    __host__ __device__ TileSums operator()(const TileSums &a, const TileSums &b) const {
+        return TileSums{a.chunks + b.chunks, a.shared + b.shared};
+    }
+};
 
-__global__ void k_tile_fill(const GroupMeta *groups, int64_t n_groups, const int32_t *h,
-                            const int32_t *off, int32_t ntx, int32_t nty, uint32_t *keys,
-                            int32_t *vals) {
-    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n_groups) return;
-    GroupMeta gm = groups[i];
-    int tx0, tx1, ty0, ty1;
-    tile_span(gm, h[gm.k], tx0, tx1, ty0, ty1);
-    int32_t o = off[i];
-    for (int ty = ty0; ty <= ty1; ++ty)
-        for (int tx = tx0; tx <= tx1; ++tx) {
-            keys[o] = (uint32_t)(((int64_t)gm.plane * nty + ty) * ntx + tx);
-            vals[o] = (int32_t)i;
-            ++o;
-        }
-}
+struct TileCounts {
+    const int32_t *tile_tp;
+    uint32_t per;
+    __device__ TileSums operator()(uint32_t t) const {
+        const uint32_t n = (uint32_t)(tile_tp[t + 1] - tile_tp[t]);
+        const uint32_t c = (n + per - 1) / per;
+        return TileSums{c, c > 1 ? 1u : 0u};
+    }
+};
 
-// Work of a (tile, group) pair: the cells its footprint covers in the tile.
-__global__ void k_pair_cost(const uint32_t *keys, const int32_t *tp_group,
-                            const GroupMeta *groups, const int32_t *h, int32_t ntx,
-                            int32_t nty, int64_t n, int32_t *cost) {
-    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    const uint32_t key = keys[i];
-    const int tx = (int)(key % (uint32_t)ntx);
-    const int ty = (int)((key / (uint32_t)ntx) % (uint32_t)nty);
-    const GroupMeta gm = groups[tp_group[i]];
-    const int hh = h[gm.k];
-    const int cx = min(gm.pu + hh + 1, (tx + 1) * kTile) - max(gm.pu - hh, tx * kTile);
-    const int cy = min(gm.pv + hh + 1, (ty + 1) * kTile) - max(gm.pv - hh, ty * kTile);
-    cost[i] = max(cx, 0) * max(cy, 0);
-}
-
-// Chunk heads: the first thread of each tile's run of (tile, group) pairs
-// (keys sorted by tile) walks the run and opens a new chunk when the current
-// one holds `per` pairs or its pairs cover more than `cmax` cells in all, so
-// that no workgroup of the gridder gets far more work than the others.  A
-// tile that fits one chunk is owned exclusively.
-__global__ void k_chunk_flags(const uint32_t *keys, const int32_t *cost, int64_t n,
-                              int32_t per, int32_t cmax, int32_t *flags) {
-    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n || (i > 0 && keys[i] == keys[i - 1])) return;
-    const uint32_t k = keys[i];
-    int count = 0, work = 0;
-    for (int64_t j = i; j < n && keys[j] == k; ++j) {
-        const int c = cost[j];
-        const bool head = count == 0 || count == per || work + c > cmax;
-        if (head && count > 0) count = work = 0;
-        flags[j] = head ? 1 : 0;
-        ++count;
-        work += c;
+// Chunks, ownership and shared list of every tile, one wavefront per tile.
+// A chunk that holds all of its tile's pairs owns the tile: it may update
+// the grid with plain loads and stores instead of atomics.
+__global__ __launch_bounds__(256) void k_tile_chunks(const int32_t *tile_tp, const TileSums *sums,
+                                                     uint32_t n_tiles, uint32_t per,
+                                                     int32_t *chunk_start, int32_t *chunk_tile,
+                                                     int32_t *chunk_excl, int32_t *tile_state,
+                                                     int32_t *shared, PlanCounts *pc) {
+    const uint32_t t = (uint32_t)(((uint64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6);
+    const uint32_t lane = threadIdx.x & 63;
+    if (t >= n_tiles) return;
+    const TileSums end = sums[t], beg = t > 0 ? sums[t - 1] : TileSums{0, 0};
+    const uint32_t n = end.chunks - beg.chunks;
+    const int32_t p0 = tile_tp[t];
+    for (uint32_t c = lane; c < n; c += 64) {
+        chunk_start[beg.chunks + c] = p0 + (int32_t)(c * per);
+        chunk_tile[beg.chunks + c] = (int32_t)t;
+        chunk_excl[beg.chunks + c] = n == 1 ? 1 : 0;
+    }
+    if (lane != 0) return;
+    tile_state[t] = n == 0 ? 0 : n == 1 ? 1 : 2;
+    if (n > 1) shared[beg.shared] = (int32_t)t;
+    if (t + 1 == n_tiles) {
+        chunk_start[end.chunks] = tile_tp[n_tiles];
+        pc->n_chunks = (int32_t)end.chunks;
+        pc->n_shared = (int32_t)end.shared;
     }
 }
 
-__global__ void k_chunk_build(const uint32_t *keys, const int32_t *flags, const int32_t *cidx,
-                              int64_t n, int32_t *chunk_start, int32_t *chunk_tile) {
-    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n || !flags[i]) return;
-    int32_t c = cidx[i];
-    chunk_start[c] = (int32_t)i;
-    chunk_tile[c] = (int32_t)keys[i];
-}
-
-// A chunk that holds all of its tile's pairs owns the tile: it may update
-// the grid with plain loads and stores instead of atomics.
-__global__ void k_chunk_excl(const uint32_t *keys, int32_t *chunk_start, int64_t n_chunks,
-                             int64_t n, int32_t *chunk_excl) {
-    int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (c >= n_chunks) return;
-    int64_t s = chunk_start[c];
-    int64_t e = (c + 1 < n_chunks) ? chunk_start[c + 1] : n;
-    bool first = (s == 0) || keys[s - 1] != keys[s];
-    bool last = (e == n) || keys[e] != keys[e - 1];
-    chunk_excl[c] = (first && last) ? 1 : 0;
-}
-
 // Work estimate of each chunk (one wavefront per chunk): the footprint
-// cells of its pairs inside the tile, complemented so that an ascending
-// sort puts the largest first; the chunk ids ride along.
+// cells of its pairs inside the tile, subtracted from the most it can be,
+// so that an ascending sort puts the largest first (in steps of 2 cells:
+// two 8-bit digits); the chunk ids ride along.  Slots past the chunks sort
+// last.
+constexpr int kCostBits = 16;
+static_assert(kChunkCells <= 2 << (kCostBits - 1), "chunk cost exceeds its sort digits");
+
 __global__ __launch_bounds__(256) void k_chunk_cost(const int32_t *chunk_start,
-                                                    const int32_t *pair_cost, int64_t n_chunks,
-                                                    uint32_t *key, int32_t *id) {
-    const int64_t c = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
+                                                    const int32_t *chunk_tile,
+                                                    const int32_t *tp_group,
+                                                    const GroupMeta *groups, int32_t ntx,
+                                                    int32_t nty, uint32_t slots,
+                                                    const PlanCounts *pc, uint32_t *key,
+                                                    int32_t *id) {
+    const uint32_t c = (uint32_t)(((uint64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6);
     const int lane = threadIdx.x & 63;
-    if (c >= n_chunks) return;
-    const int32_t s0 = chunk_start[c], n = chunk_start[c + 1] - s0;
+    if (c >= slots) return;
     uint32_t w = 0;
-    for (int i = lane; i < n; i += 64) w += (uint32_t)pair_cost[s0 + i];
+    if ((int32_t)c < pc->n_chunks) {
+        const int32_t s0 = chunk_start[c], n = chunk_start[c + 1] - s0;
+        const int tx = chunk_tile[c] % ntx, ty = (chunk_tile[c] / ntx) % nty;
+        for (int i = lane; i < n; i += 64) {
+            const GroupMeta &gm = groups[tp_group[s0 + i]];
+            const int pu = gm.pu, pv = gm.pv, h = gm.h;
+            const int cx = min(pu + h + 1, (tx + 1) * kTile) - max(pu - h, tx * kTile);
+            const int cy = min(pv + h + 1, (ty + 1) * kTile) - max(pv - h, ty * kTile);
+            w += (uint32_t)(max(cx, 0) * max(cy, 0));
+        }
+    }
     for (int off = 32; off > 0; off >>= 1) w += __shfl_xor(w, off);
     if (lane == 0) {
-        key[c] = ~w;
+        key[c] = min((uint32_t)(kChunkCells - w) >> 1, (1u << kCostBits) - 1);
         id[c] = (int32_t)c;
     }
 }
 
 // Table plane of each chunk (that of its first pair; a tile's pairs follow
 // the group order, whose keys put the frequency group and w-plane first, so
-// a chunk rarely spans two planes); the chunk ids ride along.
+// a chunk rarely spans two planes); the chunk ids ride along.  Slots past
+// the chunks get the last plane, behind its chunks (the sort is stable).
 __global__ void k_chunk_plane(const int32_t *chunk_start, const int32_t *tp_group,
-                              const GroupMeta *groups, int32_t n_w, int64_t n_chunks,
-                              uint32_t *key, int32_t *id) {
-    const int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (c >= n_chunks) return;
-    const GroupMeta &g = groups[tp_group[chunk_start[c]]];
-    key[c] = (uint32_t)(g.fg * n_w + g.k);
+                              const GroupMeta *groups, int32_t n_w, uint32_t last, uint32_t slots,
+                              const PlanCounts *pc, uint32_t *key, int32_t *id) {
+    const uint32_t c = blockIdx.x * blockDim.x + threadIdx.x;
+    if (c >= slots) return;
+    uint32_t k = last;
+    if ((int32_t)c < pc->n_chunks) {
+        const GroupMeta &g = groups[tp_group[chunk_start[c]]];
+        k = (uint32_t)(g.fg * n_w + g.k);
+    }
+    key[c] = k;
     id[c] = (int32_t)c;
-}
-
-__global__ void k_chunk_end(int32_t *chunk_start, int64_t n_chunks, int64_t n) {
-    if (threadIdx.x == 0) chunk_start[n_chunks] = (int32_t)n;
-}
-
-// Tile ownership: 1 when one exclusive chunk holds all of the tile's pairs,
-// 2 when several chunks share it (tile_state is zeroed beforehand; the
-// chunks of a shared tile all store the same value).
-__global__ void k_tile_state(const int32_t *chunk_tile, const int32_t *chunk_excl,
-                             int64_t n_chunks, int32_t *tile_state) {
-    int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (c >= n_chunks) return;
-    tile_state[chunk_tile[c]] = chunk_excl[c] ? 1 : 2;
-}
-
-// Compact list of the shared tiles (any order).
-__global__ void k_shared_list(const int32_t *tile_state, int64_t n_tiles, int32_t *list,
-                              int32_t *count) {
-    int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= n_tiles || tile_state[t] != 2) return;
-    list[atomicAdd(count, 1)] = (int32_t)t;
 }
 
 // Single-run groups: with a period L, a group whose pairs are p, p + L,
@@ -384,13 +405,34 @@ __global__ void k_single_gaps(const int32_t *order, const int32_t *gidx, int64_t
 
 // One-member groups (bit 1 of single[g]; the presum stores their sums, which
 // never need a cleared start) and the list of the other groups, which the
-// presum may add to with atomics (any order).
-__global__ void k_group_kinds(const int32_t *group_start, int64_t n_groups, int32_t *single,
-                              int32_t *multi, int32_t *count) {
-    int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (g >= n_groups) return;
-    if (group_start[g + 1] - group_start[g] == 1) single[g] |= 2;
-    else multi[atomicAdd(count, 1)] = (int32_t)g;
+// presum may add to with atomics (any order).  A wavefront takes 1024
+// groups, so that the list's end moves once per 1024.
+constexpr int kKindRounds = 16;
+
+__global__ __launch_bounds__(256) void k_group_kinds(const int32_t *group_start, int64_t n_groups,
+                                                     int32_t *single, int32_t *multi,
+                                                     PlanCounts *pc) {
+    const int lane = threadIdx.x & 63;
+    const int64_t g0 = (((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6) * (64 * kKindRounds);
+    uint64_t many[kKindRounds];
+    int total = 0;
+    for (int r = 0; r < kKindRounds; ++r) {
+        const int64_t g = g0 + r * 64 + lane;
+        const bool in = g < n_groups;
+        const bool one = in && group_start[g + 1] - group_start[g] == 1;
+        if (one) single[g] |= 2;
+        many[r] = __ballot(in && !one);
+        total += __popcll(many[r]);
+    }
+    if (total == 0) return;
+    int at = 0;
+    if (lane == 0) at = atomicAdd(&pc->n_multi, total);
+    at = __shfl(at, 0);
+    for (int r = 0; r < kKindRounds; ++r) {
+        if ((many[r] >> lane) & 1)
+            multi[at + __popcll(many[r] & ((1ull << lane) - 1))] = (int32_t)(g0 + r * 64 + lane);
+        at += __popcll(many[r]);
+    }
 }
 
 // First (tile, group) pair of every tile in the tile-sorted pair list
@@ -409,12 +451,13 @@ __global__ void k_tile_ranges(const uint32_t *keys, int64_t n, int64_t n_tiles,
 
 // Parts of the separable gridder: a tile's (tile, group) pairs in pieces of
 // at most kSepPart, so that no workgroup is left with a tile many times
-// heavier than the rest.  Keys sort the tiles by pair count, most first.
+// heavier than the rest.  Keys sort the tiles by pair count, most first
+// (counts of 65535 and more alike: such tiles are cut into equal parts).
 __global__ void k_sep_count(const int32_t *tile_tp, int64_t n_tiles, uint32_t *key,
                             int32_t *tile) {
     int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (t >= n_tiles) return;
-    key[t] = ~(uint32_t)(tile_tp[t + 1] - tile_tp[t]);
+    key[t] = 0xFFFFu - (uint32_t)min(tile_tp[t + 1] - tile_tp[t], 0xFFFF);
     tile[t] = (int32_t)t;
 }
 
@@ -429,17 +472,18 @@ __global__ void k_sep_nparts(const int32_t *tile_tp, const int32_t *tile, int64_
 
 __global__ void k_sep_fill(const int32_t *tile_tp, const int32_t *tile, const int32_t *nparts,
                            const int32_t *first, int64_t n_tiles, int4 *part, int32_t *shared,
-                           int32_t *n_shared) {
+                           PlanCounts *pc) {
     int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n_tiles) return;
     const int32_t t = tile[i], np = nparts[i];
+    if (i + 1 == n_tiles) pc->n_sep_parts = first[i] + np;
     if (np == 0) return;
     const int32_t b0 = tile_tp[t], b1 = tile_tp[t + 1];
     // equal pieces, the last one shorter by the remainder
     const int32_t len = (b1 - b0 + np - 1) / np;
     for (int q = 0; q < np; ++q)
         part[first[i] + q] = make_int4(t, b0 + q * len, min(b1, b0 + (q + 1) * len), np > 1);
-    if (np > 1) shared[atomicAdd(n_shared, 1)] = t;
+    if (np > 1) shared[atomicAdd(&pc->n_sep_shared, 1)] = t;
 }
 
 // Group of every pair in natural (row, channel) order: >= 0 kept (bit
@@ -479,34 +523,62 @@ __global__ void k_row_period(const double *uvw, int64_t nrow, int32_t rmax, int3
     atomicMin(best, r);
 }
 
-__global__ void k_taps(const GroupMeta *groups, int64_t n_groups, const int32_t *h,
-                       unsigned long long *out) {
-    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    unsigned long long t = 0;
-    if (i < n_groups) {
-        int64_t S = 2 * h[groups[i].k] + 1;
-        t = (unsigned long long)(S * S);
+// Start values of a build: counts, and (without pairs) the tile arrays.
+__global__ void k_plan_init(PlanCounts *pc, int32_t *tile_state, int32_t *tile_tp,
+                            int64_t n_tiles) {
+    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (t == 0) {
+        PlanCounts z = {};
+        z.period = kNoPeriod;
+        *pc = z;
     }
-    for (int off = 32; off > 0; off >>= 1) t += __shfl_xor(t, off);
-    if ((threadIdx.x & 63) == 0 && t) atomicAdd(out, t);
+    if (t < n_tiles) tile_state[t] = 0;
+    if (t <= n_tiles) tile_tp[t] = 0;
 }
 
 // ---------------------------------------------------------------------------
 static size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
-size_t sort_temp_bytes(int64_t n, int64_t n_tp) {
-    size_t bytes = 0, b2 = 0, sb = 0, sb2 = 0;
-    rocprim::radix_sort_pairs((void *)nullptr, bytes, (uint64_t *)nullptr,
-                              (uint64_t *)nullptr, (int32_t *)nullptr, (int32_t *)nullptr,
-                              (size_t)n, 0, 64);
-    rocprim::radix_sort_pairs((void *)nullptr, b2, (uint32_t *)nullptr,
-                              (uint32_t *)nullptr, (int32_t *)nullptr, (int32_t *)nullptr,
-                              (size_t)n_tp, 0, 32);
-    rocprim::exclusive_scan((void *)nullptr, sb, (int32_t *)nullptr, (int32_t *)nullptr,
-                            (int32_t)0, (size_t)n, rocprim::plus<int32_t>());
-    rocprim::exclusive_scan((void *)nullptr, sb2, (int32_t *)nullptr, (int32_t *)nullptr,
-                            (int32_t)0, (size_t)n_tp, rocprim::plus<int32_t>());
-    return std::max(std::max(bytes, b2), std::max(sb, sb2));
+// Radix sorts of the build.  Up to this many items the library's merge sort
+// is used, beyond it the one-sweep radix sort.
+constexpr unsigned kMergeSortMost = 1 << 15;
+using SortConfig = rocprim::radix_sort_config<rocprim::default_config, rocprim::default_config,
+                                              rocprim::default_config, kMergeSortMost>;
+
+static rocprim::transform_iterator<rocprim::counting_iterator<uint32_t>, GroupHead, uint64_t>
+group_heads(const GroupHead &f) {
+    return rocprim::transform_iterator<rocprim::counting_iterator<uint32_t>, GroupHead, uint64_t>(
+        rocprim::counting_iterator<uint32_t>(0), f);
+}
+
+static rocprim::transform_iterator<rocprim::counting_iterator<uint32_t>, TileCounts, TileSums>
+tile_counts(const TileCounts &f) {
+    return rocprim::transform_iterator<rocprim::counting_iterator<uint32_t>, TileCounts, TileSums>(
+        rocprim::counting_iterator<uint32_t>(0), f);
+}
+
+static size_t sort_temp_bytes(int64_t n, int64_t n_tp, int64_t n_tiles) {
+    size_t b[5] = {0, 0, 0, 0, 0};
+    rocprim::radix_sort_pairs<SortConfig>((void *)nullptr, b[0], (uint64_t *)nullptr,
+                                          (uint64_t *)nullptr, (int32_t *)nullptr,
+                                          (int32_t *)nullptr, (size_t)n, 0, 64);
+    rocprim::radix_sort_pairs<SortConfig>((void *)nullptr, b[1], (uint32_t *)nullptr,
+                                          (uint32_t *)nullptr, (int32_t *)nullptr,
+                                          (int32_t *)nullptr, (size_t)std::max(n_tp, n_tiles), 0,
+                                          32);
+    rocprim::inclusive_scan((void *)nullptr, b[2], group_heads(GroupHead{}), (uint64_t *)nullptr,
+                            (size_t)n, rocprim::plus<uint64_t>());
+    rocprim::inclusive_scan((void *)nullptr, b[3], tile_counts(TileCounts{}),
+                            (TileSums *)nullptr, (size_t)n_tiles, TileSumsPlus());
+    rocprim::exclusive_scan((void *)nullptr, b[4], (int32_t *)nullptr, (int32_t *)nullptr,
+                            (int32_t)0, (size_t)n_tiles, rocprim::plus<int32_t>());
+    // small sorts are not monotonic in scratch: the merge sort's most, too
+    size_t small = 0;
+    const size_t most = std::min<size_t>(kMergeSortMost, (size_t)std::max(n, n_tp));
+    rocprim::radix_sort_pairs<SortConfig>((void *)nullptr, small, (uint64_t *)nullptr,
+                                          (uint64_t *)nullptr, (int32_t *)nullptr,
+                                          (int32_t *)nullptr, most, 0, 64);
+    return std::max(small, *std::max_element(b, b + 5));
 }
 
 int64_t max_tiles_per_group(int32_t h_max) {
@@ -552,8 +624,9 @@ PlanLayout plan_layout(int64_t n_pairs, int32_t nchan, int32_t h_max, int64_t n_
     L.vals_a = take(sizeof(int32_t) * nx_);
     L.flags = take(sizeof(int32_t) * nx_);
     L.scan = take(sizeof(int32_t) * nx_);
-    L.counter = take(64);
-    L.temp = take(sort_temp_bytes(n, std::max(ntp, nt + 1)));
+    L.counter = take(sizeof(PlanCounts));
+    L.temp_bytes = sort_temp_bytes(n, ntp, nt);
+    L.temp = take(L.temp_bytes);
     L.max_tp = ntp;
     L.total = off;
     return L;
@@ -565,18 +638,19 @@ hipError_t build_plan_device(lr_plan *P, char *buf, const PlanLayout &L, const d
                              const ChanConst *d_cc, const MapGeom &g, const KeyLayout &kl,
                              const CFView &cf, const int32_t *ant1, const int32_t *ant2,
                              int32_t nant, const double *ant_dlm, double du_dl,
-                             double dv_dm, int32_t per, int32_t cmax, bool lpt, hipStream_t s) {
+                             double dv_dm, int32_t per, bool lpt, hipStream_t s) {
     hipError_t e;
-    int64_t n = P->n_pairs;
+    const int64_t n = P->n_pairs;
+    const int64_t nt = tile_count(g.nx, g.ny, g.nplane);
     uint64_t *keys_a = (uint64_t *)(buf + L.keys_a), *keys_b = (uint64_t *)(buf + L.keys_b);
     int32_t *vals_a = (int32_t *)(buf + L.vals_a);
     int32_t *order = (int32_t *)(buf + L.order);
     int32_t *flags = (int32_t *)(buf + L.flags);
+    int32_t *scan = (int32_t *)(buf + L.scan);
     int32_t *gidx = (int32_t *)(buf + L.gidx);
-    unsigned long long *counter = (unsigned long long *)(buf + L.counter);
+    PlanCounts *pc = (PlanCounts *)(buf + L.counter);
     void *temp = buf + L.temp;
-    size_t temp_bytes =
-        sort_temp_bytes(n, std::max<int64_t>(L.max_tp, tile_count(g.nx, g.ny, g.nplane) + 1));
+    size_t temp_bytes = L.temp_bytes;
     P->order = order;
     P->gidx = gidx;
     P->pair_group = (int32_t *)(buf + L.pair_group);
@@ -587,9 +661,9 @@ hipError_t build_plan_device(lr_plan *P, char *buf, const PlanLayout &L, const d
     P->chunk_start = (int32_t *)(buf + L.chunk_start);
     P->chunk_tile = (int32_t *)(buf + L.chunk_tile);
     P->chunk_excl = (int32_t *)(buf + L.chunk_excl);
-    P->chunk_order = (int32_t *)(buf + L.chunk_order);
+    P->chunk_order = nullptr;
     P->tile_state = (int32_t *)(buf + L.tile_state);
-    P->n_tiles = tile_count(g.nx, g.ny, g.nplane);
+    P->n_tiles = nt;
     P->shared_tiles = (int32_t *)(buf + L.shared_tiles);
     P->n_shared = 0;
     P->geo = (int64_t *)(buf + L.geo);
@@ -602,193 +676,134 @@ hipError_t build_plan_device(lr_plan *P, char *buf, const PlanLayout &L, const d
     P->n_sep_shared = 0;
     P->cc = d_cc;
     P->n_kept = P->n_groups = P->n_tile_pairs = P->n_chunks = P->taps = 0;
-    if ((e = launch_zero(P->tile_state, sizeof(int32_t) * P->n_tiles, s)) != hipSuccess)
-        return e;
-    if ((e = launch_zero(P->tile_tp, sizeof(int32_t) * (P->n_tiles + 1), s)) != hipSuccess)
-        return e;
-    if (n == 0) return hipSuccess;
-
-    if ((e = launch_zero(counter, 64, s)) != hipSuccess) return e;
-    hipLaunchKernelGGL(k_plan_keys, dim3(blocks(n, 256)), dim3(256), 0, s, P->nrow, P->nchan,
-                       uvw, d_cc, g, kl, ant1, ant2, nant, keys_a, vals_a, counter);
+    PlanCounts hc = {};
+    auto read_counts = [&]() {
+        hipError_t r = hipMemcpyAsync(&hc, pc, sizeof hc, hipMemcpyDeviceToHost, s);
+        return r != hipSuccess ? r : hipStreamSynchronize(s);
+    };
+    // The host waits twice: for the numbers of groups and tile pairs, which
+    // size the second half's launches, and at the end for what the calls on
+    // the plan launch by.  (One wait per count and a launch per small pass
+    // had left the GPU idle for a third of a small build.)
+    hipLaunchKernelGGL(k_plan_init, dim3(blocks(nt + 1, 256)), dim3(256), 0, s, pc,
+                       P->tile_state, P->tile_tp, nt);
+    if (n == 0) return hipGetLastError();
+    const int32_t rmax = (int32_t)std::min<int64_t>(P->nrow - 1, 1 << 16);
+    if (rmax >= 1)
+        hipLaunchKernelGGL(k_row_period, dim3(blocks(rmax, 64)), dim3(64), 0, s, uvw, P->nrow,
+                           rmax, &pc->period);
+    hipLaunchKernelGGL(k_plan_keys, dim3(blocks(n, 256)), dim3(256), 0, s, (uint32_t)n,
+                       (uint32_t)P->nchan, uvw, d_cc, g, kl, ant1, ant2, nant, keys_a, vals_a);
     if ((e = hipGetLastError()) != hipSuccess) return e;
-    e = rocprim::radix_sort_pairs(temp, temp_bytes, keys_a, keys_b, vals_a, order, (size_t)n,
-                                  0, kl.end_bit, s);
+    e = rocprim::radix_sort_pairs<SortConfig>(temp, temp_bytes, keys_a, keys_b, vals_a, order,
+                                              (size_t)n, 0, kl.end_bit, s);
     if (e != hipSuccess) return e;
-    unsigned long long nk = 0;
-    if ((e = hipMemcpyAsync(&nk, counter, sizeof nk, hipMemcpyDeviceToHost, s)) != hipSuccess)
-        return e;
-    if ((e = hipStreamSynchronize(s)) != hipSuccess) return e;
-    P->n_kept = (int64_t)nk;
+    const int32_t ntx = (g.nx + kTile - 1) / kTile, nty = (g.ny + kTile - 1) / kTile;
+    uint64_t *heads = keys_a;                   // the sort is done with its input
+    uint32_t *tk_a = (uint32_t *)flags, *tk_b = (uint32_t *)keys_b;
+    e = rocprim::inclusive_scan(temp, temp_bytes, group_heads(GroupHead{keys_b, cf.h, kl, P->merged}),
+                                heads, (size_t)n, rocprim::plus<uint64_t>(), s);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(k_group_meta, dim3(std::min(blocks(n, 256), (unsigned)kMetaBlocks)),
+                       dim3(256), 0, s, keys_b, heads, order, (uint32_t)n, (uint32_t)P->nchan, uvw,
+                       d_cc, g, cf, ant1, ant2, ant_dlm, du_dl, dv_dm, ntx, nty, gidx,
+                       P->group_start, P->groups, P->geo, tk_a, vals_a, pc);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+    if ((e = read_counts()) != hipSuccess) return e;
+    const int64_t nk = hc.n_kept, ng = hc.n_groups, ntp = (int64_t)hc.n_tile_pairs;
+    if (ntp > L.max_tp || ntp > 0x7fffffff) return hipErrorInvalidValue;
+    P->n_kept = nk;
+    P->n_groups = ng;
+    P->n_tile_pairs = ntp;
+    P->taps = (int64_t)hc.taps;
     if (nk == 0) {
         hipLaunchKernelGGL(k_pair_group, dim3(blocks(n, 256)), dim3(256), 0, s, order, gidx,
                            (const int32_t *)nullptr, (int64_t)0, n, P->pair_group);
         return hipGetLastError();
     }
+    if (hc.period != kNoPeriod) P->period = (int64_t)hc.period * P->nchan;
 
-    hipLaunchKernelGGL(k_group_flags, dim3(blocks(nk, 256)), dim3(256), 0, s, keys_b,
-                       (int64_t)nk, P->merged, flags);
-    e = rocprim::exclusive_scan(temp, temp_bytes, flags, gidx, (int32_t)0, (size_t)nk,
-                                rocprim::plus<int32_t>(), s);
-    if (e != hipSuccess) return e;
-    int32_t tail[2] = {0, 0};
-    (void)hipMemcpyAsync(&tail[0], gidx + nk - 1, 4, hipMemcpyDeviceToHost, s);
-    (void)hipMemcpyAsync(&tail[1], flags + nk - 1, 4, hipMemcpyDeviceToHost, s);
-    if ((e = hipStreamSynchronize(s)) != hipSuccess) return e;
-    P->n_groups = (int64_t)tail[0] + tail[1];
-    hipLaunchKernelGGL(k_group_meta, dim3(blocks(nk, 256)), dim3(256), 0, s, order, flags,
-                       gidx, (int64_t)nk, P->nchan, uvw, d_cc, g, cf, ant1, ant2, ant_dlm,
-                       du_dl, dv_dm, P->group_start, P->groups, P->geo);
-    hipLaunchKernelGGL(k_group_end, dim3(1), dim3(64), 0, s, P->group_start, P->n_groups,
-                       (int64_t)nk);
-    hipLaunchKernelGGL(k_group_index, dim3(blocks(nk, 256)), dim3(256), 0, s, gidx, flags,
-                       (int64_t)nk);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-
-    // (tile, group) pairs and chunks of the gridder
-    int32_t *scan = (int32_t *)(buf + L.scan);
-    uint32_t *tk_a = (uint32_t *)keys_a, *tk_b = (uint32_t *)keys_b;
-    int64_t ng = P->n_groups;
-    hipLaunchKernelGGL(k_tile_count, dim3(blocks(ng, 256)), dim3(256), 0, s, P->groups, ng,
-                       cf.h, flags);
-    e = rocprim::exclusive_scan(temp, temp_bytes, flags, scan, (int32_t)0, (size_t)ng,
-                                rocprim::plus<int32_t>(), s);
-    if (e != hipSuccess) return e;
-    (void)hipMemcpyAsync(&tail[0], scan + ng - 1, 4, hipMemcpyDeviceToHost, s);
-    (void)hipMemcpyAsync(&tail[1], flags + ng - 1, 4, hipMemcpyDeviceToHost, s);
-    if ((e = hipStreamSynchronize(s)) != hipSuccess) return e;
-    int64_t ntp = (int64_t)tail[0] + tail[1];
-    if (ntp > L.max_tp) return hipErrorInvalidValue;
-    int32_t ntx = (g.nx + kTile - 1) / kTile, nty = (g.ny + kTile - 1) / kTile;
-    hipLaunchKernelGGL(k_tile_fill, dim3(blocks(ng, 256)), dim3(256), 0, s, P->groups, ng,
-                       cf.h, scan, ntx, nty, tk_a, vals_a);
+    // (tile, group) pairs by tile, their chunks
     int end_bit = 1;
-    while (end_bit < 32 && ((int64_t)1 << end_bit) < (int64_t)g.nplane * ntx * nty) ++end_bit;
-    e = rocprim::radix_sort_pairs(temp, temp_bytes, tk_a, tk_b, vals_a, P->tp_group,
-                                  (size_t)ntp, 0, end_bit, s);
+    while (end_bit < 32 && ((int64_t)1 << end_bit) < nt) ++end_bit;
+    e = rocprim::radix_sort_pairs<SortConfig>(temp, temp_bytes, tk_a, tk_b, vals_a, P->tp_group,
+                                              (size_t)ntp, 0, end_bit, s);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_pair_cost, dim3(blocks(ntp, 256)), dim3(256), 0, s, tk_b,
-                       P->tp_group, P->groups, cf.h, ntx, nty, ntp, vals_a);
-    hipLaunchKernelGGL(k_chunk_flags, dim3(blocks(ntp, 256)), dim3(256), 0, s, tk_b, vals_a,
-                       ntp, per, cmax, flags);
-    e = rocprim::exclusive_scan(temp, temp_bytes, flags, scan, (int32_t)0, (size_t)ntp,
-                                rocprim::plus<int32_t>(), s);
+    hipLaunchKernelGGL(k_tile_ranges, dim3(blocks(nt + 1, 256)), dim3(256), 0, s, tk_b, ntp, nt,
+                       P->tile_tp);
+    TileSums *sums = (TileSums *)keys_a;
+    e = rocprim::inclusive_scan(temp, temp_bytes, tile_counts(TileCounts{P->tile_tp, (uint32_t)per}),
+                                sums, (size_t)nt, TileSumsPlus(), s);
     if (e != hipSuccess) return e;
-    (void)hipMemcpyAsync(&tail[0], scan + ntp - 1, 4, hipMemcpyDeviceToHost, s);
-    (void)hipMemcpyAsync(&tail[1], flags + ntp - 1, 4, hipMemcpyDeviceToHost, s);
-    if ((e = hipStreamSynchronize(s)) != hipSuccess) return e;
-    int64_t nch = (int64_t)tail[0] + tail[1];
-    hipLaunchKernelGGL(k_chunk_build, dim3(blocks(ntp, 256)), dim3(256), 0, s, tk_b, flags,
-                       scan, ntp, P->chunk_start, P->chunk_tile);
-    hipLaunchKernelGGL(k_chunk_excl, dim3(blocks(nch, 256)), dim3(256), 0, s, tk_b,
-                       P->chunk_start, nch, ntp, P->chunk_excl);
-    hipLaunchKernelGGL(k_chunk_end, dim3(1), dim3(64), 0, s, P->chunk_start, nch, ntp);
-    hipLaunchKernelGGL(k_tile_ranges, dim3(blocks(P->n_tiles + 1, 256)), dim3(256), 0, s, tk_b,
-                       ntp, P->n_tiles, P->tile_tp);
-    // with a kernel table the last-level cache holds, the gridder launches
-    // chunks largest first (a stable sort: ties keep tile order), so the
-    // long ones do not trail the launch; with a larger table it launches
-    // them plane by plane (tile order within a plane), so the chunks in
-    // flight read one plane of the table, which the cache holds, instead
-    // of all of them
-    if (nch > 0) {
-        int end_bits = 32;
-        if (lpt) {
-            hipLaunchKernelGGL(k_chunk_cost, dim3(blocks(nch * 64, 256)), dim3(256), 0, s,
-                               P->chunk_start, vals_a, nch, tk_a, flags);
-        } else {
-            hipLaunchKernelGGL(k_chunk_plane, dim3(blocks(nch, 256)), dim3(256), 0, s,
-                               P->chunk_start, P->tp_group, P->groups, cf.n_w, nch, tk_a, flags);
-            end_bits = 1;
-            while (end_bits < 32 && ((int64_t)1 << end_bits) < (int64_t)cf.n_fg * cf.n_w)
-                ++end_bits;
-        }
-        e = rocprim::radix_sort_pairs(temp, temp_bytes, tk_a, (uint32_t *)scan, flags,
-                                      P->chunk_order, (size_t)nch, 0, end_bits, s);
-        if (e != hipSuccess) return e;
-    } else {
-        P->chunk_order = nullptr;
-    }
-    hipLaunchKernelGGL(k_tile_state, dim3(blocks(nch, 256)), dim3(256), 0, s, P->chunk_tile,
-                       P->chunk_excl, nch, P->tile_state);
-    if ((e = launch_zero(counter, 64, s)) != hipSuccess) return e;
-    hipLaunchKernelGGL(k_shared_list, dim3(blocks(P->n_tiles, 256)), dim3(256), 0, s,
-                       P->tile_state, P->n_tiles, P->shared_tiles, (int32_t *)counter);
-    int32_t n_shared = 0;
-    (void)hipMemcpyAsync(&n_shared, counter, 4, hipMemcpyDeviceToHost, s);
-    if ((e = hipStreamSynchronize(s)) != hipSuccess) return e;
-    P->n_shared = n_shared;
-    if ((e = launch_zero(counter, 64, s)) != hipSuccess) return e;
-    hipLaunchKernelGGL(k_taps, dim3(blocks(ng, 256)), dim3(256), 0, s, P->groups, ng, cf.h,
-                       counter);
-    unsigned long long taps = 0;
-    (void)hipMemcpyAsync(&taps, counter, 8, hipMemcpyDeviceToHost, s);
-    if ((e = hipStreamSynchronize(s)) != hipSuccess) return e;
-    P->n_tile_pairs = ntp;
-    P->n_chunks = nch;
-    P->taps = (int64_t)taps;
-
-    // parts of the separable gridder, tiles with most pairs first
-    {
-        const int64_t nt = P->n_tiles;
-        uint32_t *ck_a = (uint32_t *)keys_a, *ck_b = (uint32_t *)keys_b;
-        int32_t *tid_s = (int32_t *)scan;
+    hipLaunchKernelGGL(k_tile_chunks, dim3(blocks(nt * 64, 256)), dim3(256), 0, s, P->tile_tp,
+                       sums, (uint32_t)nt, (uint32_t)per, P->chunk_start, P->chunk_tile,
+                       P->chunk_excl, P->tile_state, P->shared_tiles, pc);
+    if (sep_table(P, cf)) {
+        // parts of the separable gridder, tiles with most pairs first
+        uint32_t *ck_a = (uint32_t *)flags, *ck_b = (uint32_t *)scan;
+        int32_t *tile = (int32_t *)keys_b, *nparts = flags, *first = vals_a;
         hipLaunchKernelGGL(k_sep_count, dim3(blocks(nt, 256)), dim3(256), 0, s, P->tile_tp, nt,
                            ck_a, vals_a);
-        e = rocprim::radix_sort_pairs(temp, temp_bytes, ck_a, ck_b, vals_a, tid_s, (size_t)nt,
-                                      0, 32, s);
+        e = rocprim::radix_sort_pairs<SortConfig>(temp, temp_bytes, ck_a, ck_b, vals_a, tile,
+                                                  (size_t)nt, 0, 16, s);
         if (e != hipSuccess) return e;
         hipLaunchKernelGGL(k_sep_nparts, dim3(blocks(nt, 256)), dim3(256), 0, s, P->tile_tp,
-                           tid_s, nt, flags);
-        int32_t *first = (int32_t *)ck_a;
-        e = rocprim::exclusive_scan(temp, temp_bytes, flags, first, (int32_t)0, (size_t)nt,
+                           tile, nt, nparts);
+        e = rocprim::exclusive_scan(temp, temp_bytes, nparts, first, (int32_t)0, (size_t)nt,
                                     rocprim::plus<int32_t>(), s);
         if (e != hipSuccess) return e;
-        if ((e = launch_zero(counter, 64, s)) != hipSuccess) return e;
-        hipLaunchKernelGGL(k_sep_fill, dim3(blocks(nt, 256)), dim3(256), 0, s, P->tile_tp,
-                           tid_s, flags, first, nt, P->sep_part, P->sep_shared,
-                           (int32_t *)counter);
-        int32_t tl[3] = {0, 0, 0};
-        (void)hipMemcpyAsync(&tl[0], first + nt - 1, 4, hipMemcpyDeviceToHost, s);
-        (void)hipMemcpyAsync(&tl[1], flags + nt - 1, 4, hipMemcpyDeviceToHost, s);
-        (void)hipMemcpyAsync(&tl[2], counter, 4, hipMemcpyDeviceToHost, s);
-        if ((e = hipStreamSynchronize(s)) != hipSuccess) return e;
-        P->n_sep_parts = (int64_t)tl[0] + tl[1];
-        P->n_sep_shared = tl[2];
+        hipLaunchKernelGGL(k_sep_fill, dim3(blocks(nt, 256)), dim3(256), 0, s, P->tile_tp, tile,
+                           nparts, first, nt, P->sep_part, P->sep_shared, pc);
+    } else {
+        // with a kernel table the last-level cache holds, the gridder launches
+        // chunks largest first (a stable sort: ties keep tile order), so the
+        // long ones do not trail the launch; with a larger table it launches
+        // them plane by plane (tile order within a plane), so the chunks in
+        // flight read one plane of the table, which the cache holds, instead
+        // of all of them.  Sorted at their most possible number, so that the
+        // host need not wait for the count.
+        const uint32_t slots = (uint32_t)std::min<int64_t>(ntp, ntp / per + nt);
+        int end_bits = kCostBits;
+        if (lpt) {
+            hipLaunchKernelGGL(k_chunk_cost, dim3(blocks((int64_t)slots * 64, 256)), dim3(256), 0,
+                               s, P->chunk_start, P->chunk_tile, P->tp_group, P->groups, ntx, nty,
+                               slots, pc, tk_a, vals_a);
+        } else {
+            const int64_t planes = (int64_t)cf.n_fg * cf.n_w;
+            end_bits = 1;
+            while (end_bits < 32 && ((int64_t)1 << end_bits) < planes) ++end_bits;
+            hipLaunchKernelGGL(k_chunk_plane, dim3(blocks(slots, 256)), dim3(256), 0, s,
+                               P->chunk_start, P->tp_group, P->groups, cf.n_w,
+                               (uint32_t)planes - 1, slots, pc, tk_a, vals_a);
+        }
+        P->chunk_order = (int32_t *)(buf + L.chunk_order);
+        e = rocprim::radix_sort_pairs<SortConfig>(temp, temp_bytes, tk_a, (uint32_t *)scan, vals_a,
+                                                  P->chunk_order, (size_t)slots, 0, end_bits, s);
+        if (e != hipSuccess) return e;
     }
 
-    // the row period of the data, then the natural-order group map
-    int32_t rmax = (int32_t)std::min<int64_t>(P->nrow - 1, 1 << 16);
-    P->period = 0;
-    if (rmax >= 1) {
-        int32_t *best = (int32_t *)counter;
-        int32_t big = 0x7fffffff;
-        if ((e = upload_words(&big, sizeof big, best, s)) != hipSuccess) return e;
-        hipLaunchKernelGGL(k_row_period, dim3(blocks(rmax, 256)), dim3(256), 0, s, uvw,
-                           P->nrow, rmax, best);
-        int32_t r = big;
-        (void)hipMemcpyAsync(&r, best, 4, hipMemcpyDeviceToHost, s);
-        if ((e = hipStreamSynchronize(s)) != hipSuccess) return e;
-        if (r != big) P->period = (int64_t)r * P->nchan;
-    }
-    // groups that are one unbroken stretch of one track (pairs of another
-    // track, or a gap, break the stride L between consecutive members)
-    int32_t *single = flags;
-    hipLaunchKernelGGL(k_single_init, dim3(blocks(ng, 256)), dim3(256), 0, s, single, ng,
-                       P->period > 0 ? 1 : 0);
-    if (P->period > 0)
+    // with a row period: groups that are one unbroken stretch of one track
+    // (pairs of another track, or a gap, break the stride L between
+    // consecutive members), one-member groups, the list of the others
+    int32_t *single = nullptr;
+    if (P->period > 0) {
+        single = scan;
+        hipLaunchKernelGGL(k_single_init, dim3(blocks(ng, 256)), dim3(256), 0, s, single, ng, 1);
         hipLaunchKernelGGL(k_single_gaps, dim3(blocks(nk, 256)), dim3(256), 0, s, order, gidx,
-                           (int64_t)nk, P->period, single);
-    if ((e = launch_zero(counter, 64, s)) != hipSuccess) return e;
-    hipLaunchKernelGGL(k_group_kinds, dim3(blocks(ng, 256)), dim3(256), 0, s, P->group_start,
-                       ng, single, P->multi, (int32_t *)counter);
-    int32_t n_multi = 0;
-    (void)hipMemcpyAsync(&n_multi, counter, 4, hipMemcpyDeviceToHost, s);
-    if ((e = hipStreamSynchronize(s)) != hipSuccess) return e;
-    P->n_multi = n_multi;
+                           nk, P->period, single);
+        hipLaunchKernelGGL(k_group_kinds, dim3(blocks(ng, 256 * kKindRounds)), dim3(256), 0, s,
+                           P->group_start, ng, single, P->multi, pc);
+    }
     hipLaunchKernelGGL(k_pair_group, dim3(blocks(n, 256)), dim3(256), 0, s, order, gidx,
-                       (const int32_t *)single, (int64_t)nk, n, P->pair_group);
-    return hipGetLastError();
+                       (const int32_t *)single, nk, n, P->pair_group);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+    if ((e = read_counts()) != hipSuccess) return e;
+    P->n_chunks = hc.n_chunks;
+    P->n_shared = hc.n_shared;
+    P->n_sep_parts = hc.n_sep_parts;
+    P->n_sep_shared = hc.n_sep_shared;
+    P->n_multi = hc.n_multi;
+    return hipSuccess;
 }
 
 }  // namespace lr

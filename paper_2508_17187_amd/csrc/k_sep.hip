@@ -386,8 +386,15 @@ static hipError_t grid_sep_np(const SepArgs &sa, int64_t n_blocks, int npol, int
     }
 }
 
+// A real table with one w-plane and one frequency group: a single plane, and
+// a tile's pairs sorted by pixel row alone (the sort key puts the frequency
+// group ahead of the pixel).
+bool sep_table(const lr_plan *P, const CFView &cf) {
+    return !P->psf && !P->po && cf.real && cf.n_w == 1 && cf.n_fg == 1 && cf.h0 <= 7;
+}
+
 bool sep_gridder(const lr_plan *P, const CFView &cf, int32_t mode, bool det) {
-    if (mode == GRID_PSF || det || P->po || !cf.real || cf.n_w != 1) return false;
+    if (mode == GRID_PSF || det || !sep_table(P, cf)) return false;
     static const int forced = [] {
         const char *e = getenv("LR_GRIDDER");
         if (!e) return 0;
@@ -395,11 +402,7 @@ bool sep_gridder(const lr_plan *P, const CFView &cf, int32_t mode, bool det) {
         if (!strcmp(e, "tile")) return -1;
         return 0;
     }();
-    if (forced < 0) return false;
-    // a real table with one w-plane and one frequency group: a single plane,
-    // and a tile's pairs sorted by pixel row alone (the sort key puts the
-    // frequency group ahead of the pixel)
-    return cf.n_fg == 1 && cf.h0 <= 7;
+    return forced >= 0;
 }
 
 hipError_t launch_grid_sep(const lr_plan *P, const CFView &cf, const void *A, void *grid,

@@ -438,7 +438,7 @@ lr_status build_plan(const lr_cf *cf, const lr_vis *v, int psf, void *buf, size_
     // one kind's table is read per gridder pass
     const bool lpt = (size_t)cf->kind_elems * cf->elem_bytes <= ((size_t)256 << 20);
     e = build_plan_device(P, b, L, v->uvw, d_cc, g, kl, view_of(cf), v->ant1, v->ant2,
-                          v->nant, v->ant_dlm, du_dl, dv_dm, chunk_pairs(), kChunkCells, lpt, s);
+                          v->nant, v->ant_dlm, du_dl, dv_dm, chunk_pairs(), lpt, s);
     if (e == hipErrorInvalidValue)
         return fail(LR_E_RANGE, "plan tile table overflow");
     if (e != hipSuccess) return dev_fail(e, "plan build");

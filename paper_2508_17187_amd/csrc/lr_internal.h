@@ -17,10 +17,9 @@ constexpr double kCLight = 299792458.0;
 constexpr int kMaxChanPerUpload = 48;
 constexpr int kTile = 32;          // gridder tile side (cells)
 constexpr int kChunkMax = 64;      // most (tile, group) pairs per gridder workgroup
-// most footprint cells per workgroup: a pair covers at most one tile, so
-// this cap binds only below kChunkMax pairs of whole-tile footprints (a cap
-// of 32 tiles cost the large A+W image 7% of its gridder time in extra
-// atomic flushes, with no gain on 2048^2 grids)
+// most footprint cells a workgroup can get: a pair covers at most one tile (a
+// cap of 32 tiles per chunk cost the large A+W image 7% of its gridder time
+// in extra atomic flushes, with no gain on 2048^2 grids)
 constexpr int kChunkCells = kChunkMax * kTile * kTile;
 constexpr int32_t kSingleRun = 1 << 30;   // pair_group flag: the group is one stretch of a track
 constexpr int32_t kSingleton = 1 << 29;   // pair_group flag: the group has one member

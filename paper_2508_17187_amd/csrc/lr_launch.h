@@ -18,9 +18,17 @@ struct PlanLayout {
     size_t chan, order, gidx, pair_group, group_start, groups, tp_group, chunk_start, chunk_tile,
         chunk_excl, chunk_order, tile_state, shared_tiles, geo, tile_tp, multi, sep_part,
         sep_shared, persistent;
-    size_t keys_a, keys_b, vals_a, flags, scan, counter, temp;
+    size_t keys_a, keys_b, vals_a, flags, scan, counter, temp, temp_bytes;
     int64_t max_tp;
     size_t total;
+};
+
+// Counts a plan build keeps on the device and reads back twice.
+constexpr int32_t kNoPeriod = 0x7fffffff;
+struct PlanCounts {
+    unsigned long long taps, n_tile_pairs;
+    int32_t n_kept, n_groups, period;
+    int32_t n_chunks, n_shared, n_sep_parts, n_sep_shared, n_multi;
 };
 
 hipError_t upload_chan(const std::vector<ChanConst> &cc, ChanConst *d, hipStream_t s);
@@ -28,7 +36,6 @@ hipError_t upload_words(const void *src, size_t bytes, void *d, hipStream_t s);
 hipError_t launch_debug_map(int64_t nrow, int32_t nchan, const double *uvw,
                             const std::vector<ChanConst> &cc, const MapGeom &g, int32_t *out,
                             hipStream_t s);
-size_t sort_temp_bytes(int64_t n, int64_t n_tp);
 int64_t max_tiles_per_group(int32_t h_max);
 PlanLayout plan_layout(int64_t n_pairs, int32_t nchan, int32_t h_max, int64_t n_tiles);
 int64_t tile_count(int32_t nx, int32_t ny, int32_t nplane);
@@ -36,7 +43,7 @@ hipError_t build_plan_device(lr_plan *P, char *buf, const PlanLayout &L, const d
                              const ChanConst *d_cc, const MapGeom &g, const KeyLayout &kl,
                              const CFView &cf, const int32_t *ant1, const int32_t *ant2,
                              int32_t nant, const double *ant_dlm, double du_dl,
-                             double dv_dm, int32_t per, int32_t cmax, bool lpt, hipStream_t s);
+                             double dv_dm, int32_t per, bool lpt, hipStream_t s);
 
 // ---- CF build (k_cf.hip) -----------------------------------------------------
 struct CFBuildArgs {
@@ -78,6 +85,8 @@ hipError_t launch_grid(const lr_plan *P, const CFView &cf, const void *A, void *
 // workgroup per tile, every cell written once): then GRID_SET needs no
 // clearing of shared tiles beforehand.
 bool sep_gridder(const lr_plan *P, const CFView &cf, int32_t mode, bool det);
+// Whether some call on this plan takes it (its parts are then part of the plan).
+bool sep_table(const lr_plan *P, const CFView &cf);
 // The separable gridder's launch (k_sep.hip), when sep_gridder() chose it.
 hipError_t launch_grid_sep(const lr_plan *P, const CFView &cf, const void *A, void *grid,
                            int precision, int32_t npol, int32_t nx, int32_t ny, bool set,
