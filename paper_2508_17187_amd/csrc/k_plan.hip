@@ -285,11 +285,12 @@ __global__ __launch_bounds__(256) void k_group_meta(
 struct TileSums {
     uint32_t chunks;      // gridder chunks
     uint32_t shared;      // tiles with several chunks
+    uint32_t used;        // tiles with pairs
 };
 
 struct TileSumsPlus {
     __host__ __device__ TileSums operator()(const TileSums &a, const TileSums &b) const {
-        return TileSums{a.chunks + b.chunks, a.shared + b.shared};
+        return TileSums{a.chunks + b.chunks, a.shared + b.shared, a.used + b.used};
     }
 };
 
@@ -299,7 +300,7 @@ struct TileCounts {
     __device__ TileSums operator()(uint32_t t) const {
         const uint32_t n = (uint32_t)(tile_tp[t + 1] - tile_tp[t]);
         const uint32_t c = (n + per - 1) / per;
-        return TileSums{c, c > 1 ? 1u : 0u};
+        return TileSums{c, c > 1 ? 1u : 0u, c > 0 ? 1u : 0u};
     }
 };
 
@@ -314,7 +315,7 @@ __global__ __launch_bounds__(256) void k_tile_chunks(const int32_t *tile_tp, con
     const uint32_t t = (uint32_t)(((uint64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6);
     const uint32_t lane = threadIdx.x & 63;
     if (t >= n_tiles) return;
-    const TileSums end = sums[t], beg = t > 0 ? sums[t - 1] : TileSums{0, 0};
+    const TileSums end = sums[t], beg = t > 0 ? sums[t - 1] : TileSums{0, 0, 0};
     const uint32_t n = end.chunks - beg.chunks;
     const int32_t p0 = tile_tp[t];
     for (uint32_t c = lane; c < n; c += 64) {
@@ -451,7 +452,17 @@ __global__ void k_tile_ranges(const uint32_t *keys, int64_t n, int64_t n_tiles,
 
 // Parts of the separable gridder: a tile's (tile, group) pairs in pieces of
 // at most kSepPart, so that no workgroup is left with a tile many times
-// heavier than the rest.  Keys sort the tiles by pair count, most first
+// heavier than the rest.  A wavefront takes its pairs one after another
+// (about 60 ns each in FP64), so when the data fall on few tiles the longest
+// part is the call: the compact 22,464-sample observation on 4 tiles of a
+// 256^2 grid took 356 us whole and takes 29 us in parts of 64.  Fewer than
+// `few` tiles with pairs are therefore cut so finely that there are about
+// kSepFill parts.  The line lies at 1024 tiles for supports up to 7 (4 per
+// CU; W-projection tracks on 1024^2, about 500 tiles: 414 -> 177 us; on
+// 2048^2, above it, parts would cost more in atomic flushes than they
+// balance, 108 -> 118 us) and lower by the number of taps a lane holds, since
+// wider supports keep a SIMD busy with fewer wavefronts (support 15: 800 ->
+// 585 us on 512^2, but 975 -> 1081 us on 1024^2).  Keys sort the tiles by pair count, most first
 // (counts of 65535 and more alike: such tiles are cut into equal parts).
 __global__ void k_sep_count(const int32_t *tile_tp, int64_t n_tiles, uint32_t *key,
                             int32_t *tile) {
@@ -461,13 +472,16 @@ __global__ void k_sep_count(const int32_t *tile_tp, int64_t n_tiles, uint32_t *k
     tile[t] = (int32_t)t;
 }
 
-__global__ void k_sep_nparts(const int32_t *tile_tp, const int32_t *tile, int64_t n_tiles,
-                             int32_t *nparts) {
+__global__ void k_sep_nparts(const int32_t *tile_tp, const int32_t *tile, const TileSums *sums,
+                             int64_t n_tiles, int32_t few, int32_t *nparts) {
     int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n_tiles) return;
+    int32_t most = kSepPart;
+    if ((int)sums[n_tiles - 1].used < few)
+        most = max(kSepPartMin, min(kSepPart, (tile_tp[n_tiles] + kSepFill - 1) / kSepFill));
     const int32_t t = tile[i];
     const int32_t n = tile_tp[t + 1] - tile_tp[t];
-    nparts[i] = (n + kSepPart - 1) / kSepPart;
+    nparts[i] = (n + most - 1) / most;
 }
 
 __global__ void k_sep_fill(const int32_t *tile_tp, const int32_t *tile, const int32_t *nparts,
@@ -613,7 +627,7 @@ PlanLayout plan_layout(int64_t n_pairs, int32_t nchan, int32_t h_max, int64_t n_
     L.tile_tp = take(sizeof(int32_t) * (std::max<int64_t>(n_tiles, 1) + 1));
     L.multi = take(sizeof(int32_t) * n);
     const int64_t nt = std::max<int64_t>(n_tiles, 1);
-    L.sep_part = take(sizeof(int4) * (nt + ntp / kSepPart + 1));
+    L.sep_part = take(sizeof(int4) * (nt + ntp / kSepPart + kSepFill + 1));
     L.sep_shared = take(sizeof(int32_t) * nt);
     L.persistent = off;
     // transient (the tile sort of the separable gridder's parts needs
@@ -742,13 +756,14 @@ hipError_t build_plan_device(lr_plan *P, char *buf, const PlanLayout &L, const d
         // parts of the separable gridder, tiles with most pairs first
         uint32_t *ck_a = (uint32_t *)flags, *ck_b = (uint32_t *)scan;
         int32_t *tile = (int32_t *)keys_b, *nparts = flags, *first = vals_a;
+        const int32_t S = 2 * cf.h0 + 1;
         hipLaunchKernelGGL(k_sep_count, dim3(blocks(nt, 256)), dim3(256), 0, s, P->tile_tp, nt,
                            ck_a, vals_a);
         e = rocprim::radix_sort_pairs<SortConfig>(temp, temp_bytes, ck_a, ck_b, vals_a, tile,
                                                   (size_t)nt, 0, 16, s);
         if (e != hipSuccess) return e;
         hipLaunchKernelGGL(k_sep_nparts, dim3(blocks(nt, 256)), dim3(256), 0, s, P->tile_tp,
-                           tile, nt, nparts);
+                           tile, sums, nt, kSepFill / ((S * S + 63) / 64), nparts);
         e = rocprim::exclusive_scan(temp, temp_bytes, nparts, first, (int32_t)0, (size_t)nt,
                                     rocprim::plus<int32_t>(), s);
         if (e != hipSuccess) return e;

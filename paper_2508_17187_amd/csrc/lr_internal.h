@@ -25,6 +25,8 @@ constexpr int32_t kSingleRun = 1 << 30;   // pair_group flag: the group is one s
 constexpr int32_t kSingleton = 1 << 29;   // pair_group flag: the group has one member
 constexpr int32_t kGroupFlags = kSingleRun | kSingleton;
 constexpr int kSepPart = 4096;     // most (tile, group) pairs per workgroup of the separable gridder
+constexpr int kSepPartMin = 64;    // shortest part when few tiles hold all pairs
+constexpr int kSepFill = 1024;     // parts that fill the chip
 
 // ---------------------------------------------------------------------------
 // Per-channel constants formed on the host in FP64 (no contraction).

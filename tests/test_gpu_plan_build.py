@@ -76,6 +76,28 @@ def test_chunk_edges(n):
     assert info["taps"] == 49 * info["n_groups"]
 
 
+@pytest.mark.parametrize("h", [1, 3, 4, 6, 7])
+@pytest.mark.parametrize("form", ["f64", "f32"])
+def test_few_tiles_in_many_parts(h, form):
+    """Dense data on few tiles: the separable gridder's tiles are cut into
+    parts that add to shared tiles, accumulating and overwriting."""
+    prec = lr.PRECISIONS[form]
+    wl = synth.tiny_workload(n_ant=9, n_time=150, dt_s=90.0, nchan=3, npol=2, nx=160, ny=100,
+                             cell_arcsec=20.0, diameter_m=1500.0, oversample=32, terms=TERM_PS,
+                             h_min=h, h_max=h, cfg_id=273)
+    cf = W.build_cf(wl, prec)
+    v = W.device_vis(wl, prec)
+    v.plan = lr.Plan(cf, v)
+    ref = Problem.from_workload(wl, oracle.build_cf(wl.grid, wl.cf)).grid(wl.vis, wl.weight)
+    tol = {"f64": 1e-12, "f32": 1e-5}[form] * np.linalg.norm(ref)
+    g = W.empty_grid(wl, prec)
+    lr.lr_grid(cf, v, prec, g)
+    assert np.linalg.norm(g.cpu().numpy() - ref) <= tol
+    g.fill_(complex("nan"))
+    lr.lr_grid_overwrite(cf, v, prec, g)
+    assert np.linalg.norm(g.cpu().numpy() - ref) <= tol
+
+
 def test_no_pair_kept():
     wl = lattice(6)
     wl.obs.uvw[:, 0] = 1e6
