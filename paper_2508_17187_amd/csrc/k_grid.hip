@@ -207,18 +207,20 @@ __global__ __launch_bounds__(256) void k_presum(
 // DET (deterministic order) stores those groups and sets done[g], and adds
 // nothing with atomics: the other groups are summed again afterwards, in a
 // fixed order, by k_presum_seg and k_presum_join.
-constexpr int kColW = 8, kColT = 8, kColBlocks = 16;
+constexpr int kColW = 8, kColT = 8, kColBlocks = 16;   // kColBlocks: most blocks of steps
 
-template <typename T, int NPOL, bool UNIT, bool SUMS, bool DET>
+// FULL: kColBlocks blocks of steps, known to the compiler (large data).
+template <typename T, int NPOL, bool UNIT, bool SUMS, bool DET, bool FULL>
 __global__ __launch_bounds__(256) void k_presum_col(
-    int64_t n_pairs, int64_t L, int64_t ncb, const int32_t *pair_group,
+    int64_t n_pairs, int64_t L, int64_t ncb, int32_t step_blocks, const int32_t *pair_group,
     const GroupMeta *groups, const T *vis, const T *weight, cpx<T> *A, double *sumwt,
     long long *counters, uint8_t *done) {
     const int lane = threadIdx.x & 63;
+    const int n_blocks = FULL ? kColBlocks : step_blocks;
     const int64_t wave = (int64_t)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
     const int cl = lane & (kColW - 1), tl = lane / kColW;
     const int64_t c = (wave % ncb) * kColW + cl;
-    const int64_t mw = (wave / ncb) * (kColT * kColBlocks);
+    const int64_t mw = (wave / ncb) * (kColT * n_blocks);
     // lanes of my column, and of my column before me, in a ballot
     const uint64_t colmask = 0x0101010101010101ull << cl;
     const uint64_t below = colmask & ((1ull << lane) - 1);
@@ -272,9 +274,9 @@ __global__ __launch_bounds__(256) void k_presum_col(
     };
     Step nxt;
     fetch(0, nxt);
-    for (int b = 0; b < kColBlocks; ++b) {
+    for (int b = 0; b < n_blocks; ++b) {
         const Step cur = nxt;
-        if (b + 1 < kColBlocks) fetch(b + 1, nxt);
+        if (b + 1 < n_blocks) fetch(b + 1, nxt);
         cpx<T> a[NPOL];
         for (int p = 0; p < NPOL; ++p) a[p] = {(T)0, (T)0};
         const bool single = cur.g >= 0 && (cur.g & kSingleRun);
@@ -356,13 +358,21 @@ __global__ __launch_bounds__(256) void k_presum_col(
     add_totals<NPOL, kColT>(kept, flagged, dropped, sw, plane, sumwt, counters);
 }
 
-// Work shape of the track presum: ncb column blocks x ceil(M / 64) step
-// blocks, one wavefront each.
-static void col_shape(int64_t n_pairs, int64_t L, int64_t &ncb, int64_t &blocks) {
+// Work shape of the track presum: ncb column blocks x ceil(M / (8 n_blocks))
+// step blocks, one wavefront each.  A wavefront walks its blocks of steps one
+// after another (about 1 us each), and runs that cross wavefronts end in
+// atomics, so it takes as many (up to 16) as leave kColWaves wavefronts, 8
+// per CU: 22,464 samples then go through 352 wavefronts of one block, not 44
+// of sixteen (gridding call 27 -> 20 us), and 3.4 M pairs keep 16.
+constexpr int64_t kColWaves = 2048;
+
+static void col_shape(int64_t n_pairs, int64_t L, int64_t &ncb, int32_t &n_blocks,
+                      int64_t &blocks) {
     int64_t M = (n_pairs + L - 1) / L;
     ncb = (L + kColW - 1) / kColW;
-    const int64_t span = kColT * kColBlocks;
-    int64_t waves = ncb * ((M + span - 1) / span);
+    const int64_t steps = (M + kColT - 1) / kColT;
+    n_blocks = (int32_t)std::max<int64_t>(1, std::min<int64_t>(kColBlocks, ncb * steps / kColWaves));
+    int64_t waves = ncb * ((steps + n_blocks - 1) / n_blocks);
     blocks = (waves + 3) / 4;
 }
 
@@ -861,19 +871,24 @@ static hipError_t presum_t(const lr_plan *P, const VisArgs &v, void *A, double *
     long long *cnt = (long long *)counters;
     if (P->period > 0) {
         int64_t ncb, nb;
-        col_shape(P->n_pairs, P->period, ncb, nb);
+        int32_t sb;
+        col_shape(P->n_pairs, P->period, ncb, sb, nb);
         dim3 g2((unsigned)nb);
         if (!sums)
-            hipLaunchKernelGGL((k_presum_col<T, NPOL, false, false, false>), g2, blk, 0, s,
-                               P->n_pairs, P->period, ncb, P->pair_group, P->groups, vis, wt,
+            hipLaunchKernelGGL((k_presum_col<T, NPOL, false, false, false, false>), g2, blk, 0, s,
+                               P->n_pairs, P->period, ncb, sb, P->pair_group, P->groups, vis, wt,
                                (cpx<T> *)A, sumwt, cnt, nullptr);
         else if (v.unit_vis)
-            hipLaunchKernelGGL((k_presum_col<T, NPOL, true, true, false>), g2, blk, 0, s,
-                               P->n_pairs, P->period, ncb, P->pair_group, P->groups, vis, wt,
+            hipLaunchKernelGGL((k_presum_col<T, NPOL, true, true, false, false>), g2, blk, 0, s,
+                               P->n_pairs, P->period, ncb, sb, P->pair_group, P->groups, vis, wt,
+                               (cpx<T> *)A, sumwt, cnt, nullptr);
+        else if (sb == kColBlocks)
+            hipLaunchKernelGGL((k_presum_col<T, NPOL, false, true, false, true>), g2, blk, 0, s,
+                               P->n_pairs, P->period, ncb, sb, P->pair_group, P->groups, vis, wt,
                                (cpx<T> *)A, sumwt, cnt, nullptr);
         else
-            hipLaunchKernelGGL((k_presum_col<T, NPOL, false, true, false>), g2, blk, 0, s,
-                               P->n_pairs, P->period, ncb, P->pair_group, P->groups, vis, wt,
+            hipLaunchKernelGGL((k_presum_col<T, NPOL, false, true, false, false>), g2, blk, 0, s,
+                               P->n_pairs, P->period, ncb, sb, P->pair_group, P->groups, vis, wt,
                                (cpx<T> *)A, sumwt, cnt, nullptr);
         return hipGetLastError();
     }
@@ -1063,11 +1078,12 @@ static hipError_t presum_det_t(const lr_plan *P, const VisArgs &v, void *A, uint
         // the column presum stores the groups it holds whole (and counts the
         // samples: integer atomics are exact); the rest are summed below
         int64_t ncb, nb;
-        col_shape(P->n_pairs, P->period, ncb, nb);
+        int32_t sb;
+        col_shape(P->n_pairs, P->period, ncb, sb, nb);
         hipLaunchKernelGGL(k_clear_u8, dim3(nblk(P->n_groups, 256)), blk, 0, s, done,
                            P->n_groups);
-        hipLaunchKernelGGL((k_presum_col<T, NPOL, false, true, true>), dim3((unsigned)nb), blk,
-                           0, s, P->n_pairs, P->period, ncb, P->pair_group, P->groups, vis, wt,
+        hipLaunchKernelGGL((k_presum_col<T, NPOL, false, true, true, false>), dim3((unsigned)nb), blk,
+                           0, s, P->n_pairs, P->period, ncb, sb, P->pair_group, P->groups, vis, wt,
                            (cpx<T> *)A, (double *)nullptr, (long long *)counters, done);
     } else if (counters) {
         VisArgs w{nullptr, v.weight, v.npol, 0};
