@@ -191,6 +191,11 @@ __device__ __forceinline__ int64_t uni64(int64_t v) {
     return (int64_t)(((uint64_t)hi << 32) | lo);
 }
 
+// -1 for a group whose sub-kernel is mirrored into an odd kind's negative.
+__device__ __forceinline__ bool negated(const CFView &cf, int form) {
+    return cf.odd && ((form & kFlipU) != 0) != ((form & kFlipV) != 0);
+}
+
 template <typename T>
 __device__ __forceinline__ void cmac(cpx<T> &acc, const cpx<T> &c, const cpx<T> &a) {
     acc.x = fma(c.x, a.x, acc.x);

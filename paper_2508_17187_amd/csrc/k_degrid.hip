@@ -22,7 +22,8 @@ struct DegridArgs {
 // correlation q gets the sum of the pols p its mask bits select, added to
 // what earlier passes left when accum is set.
 template <typename T, int NPOL>
-__device__ __forceinline__ void store_group(const DegridArgs &a, int64_t g, const cpx<T> (&v)[NPOL]) {
+__device__ __forceinline__ void store_group(const DegridArgs &a, int64_t g, int form,
+                                            const cpx<T> (&v)[NPOL]) {
     cpx<T> *out = (cpx<T> *)a.Vg + g * NPOL;
     for (int q = 0; q < NPOL; ++q) {
         cpx<T> r;
@@ -35,6 +36,7 @@ __device__ __forceinline__ void store_group(const DegridArgs &a, int64_t g, cons
                     r.x += v[p].x;
                     r.y += v[p].y;
                 }
+            if (negated(a.cf, form)) r = {-r.x, -r.y};
         }
         if (a.accum) {
             r.x += out[q].x;
@@ -68,7 +70,8 @@ __global__ __launch_bounds__(256) void k_degrid(DegridArgs a) {
     const int S = 2 * h + 1;
     const int SS = S * S;
     const float sc = a.cf.scale[(int64_t)gm.fg * a.cf.n_w + gm.k];
-    const bool cj = uni(gm.conj) != 0;
+    const int form = uni(gm.form);
+    const bool cj = (form & kConj) != 0;
     const char *cfb = (const char *)a.cf.table + uni64(gm.cf_off) * E;
     // corner cell (tap (0, 0)) of pol 0
     const int64_t corner = uni64(gm.cell) - (int64_t)h * a.nx - h;
@@ -81,8 +84,13 @@ __global__ __launch_bounds__(256) void k_degrid(DegridArgs a) {
     const int row = a.nx * (int)(2 * sizeof(T));          // bytes per grid row
     // lane's first tap and the per-step advance of 64 taps
     const int dty = 64 / S, dtx = 64 - dty * S;
+    // taps in the order the sub-kernel stores them; on flipped axes the grid
+    // (and the tap's coordinate) runs backwards
+    const int scol = form & kFlipU ? -(int)(2 * sizeof(T)) : (int)(2 * sizeof(T));
+    const int srow = form & kFlipV ? -row : row;
     int ty = lane / S, tx = lane - (lane / S) * S;
-    int goff = ty * row + tx * (int)(2 * sizeof(T));
+    int goff = (form & kFlipV ? (S - 1) * row : 0) +
+               (form & kFlipU ? (S - 1) * (int)(2 * sizeof(T)) : 0) + ty * srow + tx * scol;
     cpx<T> sum[NPOL];
     for (int p = 0; p < NPOL; ++p) sum[p] = {(T)0, (T)0};
     for (int t0 = 0; t0 < SS; t0 += 64 * NT) {
@@ -93,8 +101,8 @@ __global__ __launch_bounds__(256) void k_degrid(DegridArgs a) {
         for (int u = 0; u < NT; ++u) {
             const int tap = t0 + u * 64 + lane;
             ok[u] = tap < SS;
-            txs[u] = tx;
-            tys[u] = ty;
+            txs[u] = form & kFlipU ? S - 1 - tx : tx;
+            tys[u] = form & kFlipV ? S - 1 - ty : ty;
             // every lane loads (a lane past the footprint reads tap 0, in
             // bounds, and adds nothing): loads outside divergent branches
             // let the waits count down tap by tap
@@ -108,11 +116,11 @@ __global__ __launch_bounds__(256) void k_degrid(DegridArgs a) {
             // advance by 64 taps
             tx += dtx;
             ty += dty;
-            goff += dty * row + dtx * (int)(2 * sizeof(T));
+            goff += dty * srow + dtx * scol;
             if (tx >= S) {
                 tx -= S;
                 ++ty;
-                goff += row - S * (int)(2 * sizeof(T));
+                goff += srow - S * scol;
             }
         }
         for (int u = 0; u < NT; ++u) {
@@ -133,7 +141,7 @@ __global__ __launch_bounds__(256) void k_degrid(DegridArgs a) {
     }
     cpx<T> tot[NPOL];
     for (int p = 0; p < NPOL; ++p) tot[p] = {wave_sum(sum[p].x), wave_sum(sum[p].y)};
-    if (lane == 0) store_group<T, NPOL>(a, g, tot);
+    if (lane == 0) store_group<T, NPOL>(a, g, form, tot);
 }
 
 // FP32 grids without a pointing phasor: lanes over pairs of neighbouring
@@ -161,12 +169,19 @@ __global__ __launch_bounds__(256) void k_degrid_pair(DegridArgs a) {
     const int h = uni(gm.h);
     const int S = 2 * h + 1;
     const float sc = a.cf.scale[(int64_t)gm.fg * a.cf.n_w + gm.k];
-    const bool cj = uni(gm.conj) != 0;
+    const int form = uni(gm.form);
+    const bool cj = (form & kConj) != 0;
     const int lead = (uni(gm.pu) - h) & 1;              // footprint starts at an odd column
     const int W2 = (S + lead + 1) >> 1;                 // pairs per footprint row
     const int NP = S * W2;
-    // kernel bytes from tap (0, -lead); grid cell (0, -lead) of pol 0
-    const char *cfb = (const char *)a.cf.table + (uni64(gm.cf_off) - lead) * E;
+    // kernel elements from one before the sub-kernel; the pair of row r and
+    // columns (2 c - lead, 2 c - lead + 1) starts at element k0 + r sv + c su,
+    // where a flipped row holds the pair's two values in reverse order.
+    // grid cell (0, -lead) of pol 0
+    const char *cfb = (const char *)a.cf.table + (uni64(gm.cf_off) - 1) * E;
+    const bool fu = (form & kFlipU) != 0;
+    const int su = fu ? -2 : 2, sv = form & kFlipV ? -S : S;
+    const int k0 = 1 + (fu ? S - 2 + lead : -lead) + (form & kFlipV ? (S - 1) * S : 0);
     const int64_t corner = uni64(gm.cell) - (int64_t)h * a.nx - h - lead;
     const int64_t pstride = a.pol_stride * 8;
     const char *gbp[NPOL];
@@ -188,7 +203,7 @@ __global__ __launch_bounds__(256) void k_degrid_pair(DegridArgs a) {
             v0[u] = ok[u] && tu0 >= 0;
             v1[u] = ok[u] && tu0 + 1 < S;
             // lanes past the footprint load pair 0 (in bounds) and add nothing
-            const uint32_t co = ok[u] ? (uint32_t)(r * S + 2 * c) * (uint32_t)E : 0u;
+            const uint32_t co = ok[u] ? (uint32_t)(k0 + r * sv + c * su) * (uint32_t)E : 0u;
             const uint32_t go = ok[u] ? (uint32_t)(r * row + c * 16) : 0u;
             cr[u] = *(const Raw2 *)(cfb + co);
             for (int p = 0; p < NPOL; ++p) gv[u][p] = *(const f32x4_a8 *)(gbp[p] + go);
@@ -201,38 +216,43 @@ __global__ __launch_bounds__(256) void k_degrid_pair(DegridArgs a) {
         }
         for (int u = 0; u < NT; ++u) {
             // the pair's two kernel values, zero outside the footprint row
-            cpx<float> k0, k1;
+            cpx<float> c0, c1;
             if constexpr (E == 8) {
-                k0 = {cr[u].x, cr[u].y};
-                k1 = {cr[u].z, cr[u].w};
+                c0 = {cr[u].x, cr[u].y};
+                c1 = {cr[u].z, cr[u].w};
             } else {
-                k0 = CFRaw<ST>::decode((Raw)cr[u].x, sc);
-                k1 = CFRaw<ST>::decode((Raw)cr[u].y, sc);
+                c0 = CFRaw<ST>::decode((Raw)cr[u].x, sc);
+                c1 = CFRaw<ST>::decode((Raw)cr[u].y, sc);
             }
-            if (RE) k0.y = k1.y = 0.f;
-            if (!v0[u]) k0 = {0.f, 0.f};
-            if (!v1[u]) k1 = {0.f, 0.f};
+            if (fu) {
+                const cpx<float> t = c0;
+                c0 = c1;
+                c1 = t;
+            }
+            if (RE) c0.y = c1.y = 0.f;
+            if (!v0[u]) c0 = {0.f, 0.f};
+            if (!v1[u]) c1 = {0.f, 0.f};
             if (cj) {
-                k0.y = -k0.y;
-                k1.y = -k1.y;
+                c0.y = -c0.y;
+                c1.y = -c1.y;
             }
             for (int p = 0; p < NPOL; ++p) {
                 const cpx<float> g0 = {gv[u][p].x, gv[u][p].y}, g1 = {gv[u][p].z, gv[u][p].w};
                 if constexpr (RE) {
-                    sum[p].x = fmaf(k0.x, g0.x, sum[p].x);
-                    sum[p].y = fmaf(k0.x, g0.y, sum[p].y);
-                    sum[p].x = fmaf(k1.x, g1.x, sum[p].x);
-                    sum[p].y = fmaf(k1.x, g1.y, sum[p].y);
+                    sum[p].x = fmaf(c0.x, g0.x, sum[p].x);
+                    sum[p].y = fmaf(c0.x, g0.y, sum[p].y);
+                    sum[p].x = fmaf(c1.x, g1.x, sum[p].x);
+                    sum[p].y = fmaf(c1.x, g1.y, sum[p].y);
                 } else {
-                    cmac_conj(sum[p], k0, g0);
-                    cmac_conj(sum[p], k1, g1);
+                    cmac_conj(sum[p], c0, g0);
+                    cmac_conj(sum[p], c1, g1);
                 }
             }
         }
     }
     cpx<float> tot[NPOL];
     for (int p = 0; p < NPOL; ++p) tot[p] = {wave_sum(sum[p].x), wave_sum(sum[p].y)};
-    if (lane == 0) store_group<float, NPOL>(a, g, tot);
+    if (lane == 0) store_group<float, NPOL>(a, g, form, tot);
 }
 
 // Small supports (S <= 2 kDegridSmallH + 1): a 7 x 7 footprint would leave
@@ -247,6 +267,7 @@ __global__ __launch_bounds__(256) void k_degrid_small(DegridArgs a) {
     const int sub = threadIdx.x & 15;
     const int64_t g = (int64_t)blockIdx.x * (blockDim.x >> 4) + (threadIdx.x >> 4);
     const bool live = g < a.n_groups;
+    int form = 0;
     cpx<T> sum[NPOL];
     for (int p = 0; p < NPOL; ++p) sum[p] = {(T)0, (T)0};
     if (live) {
@@ -257,6 +278,9 @@ __global__ __launch_bounds__(256) void k_degrid_small(DegridArgs a) {
         const float invS = 1.0f / (float)S;
         const float sc = a.cf.scale[(int64_t)gm.fg * a.cf.n_w + gm.k];
         const char *cfb = (const char *)a.cf.table + gm.cf_off * E;
+        form = gm.form;
+        // taps in storage order; on flipped axes the grid runs backwards
+        const bool fu = (form & kFlipU) != 0, fv = (form & kFlipV) != 0;
         const int64_t corner = gm.cell - (int64_t)h * a.nx - h;
         const T *grid = (const T *)a.grid;
         for (int t0 = 0; t0 < SS; t0 += 64) {
@@ -267,6 +291,8 @@ __global__ __launch_bounds__(256) void k_degrid_small(DegridArgs a) {
                 const int tap = t0 + u * 16 + sub;
                 int ty, tx;
                 divmod_small(tap, S, invS, ty, tx);
+                if (fu) tx = S - 1 - tx;
+                if (fv) ty = S - 1 - ty;
                 tys[u] = ty;
                 txs[u] = tx;
                 // every lane loads (past the footprint: tap 0, in bounds,
@@ -290,7 +316,7 @@ __global__ __launch_bounds__(256) void k_degrid_small(DegridArgs a) {
                 } else {
                     cpx<T> cv = CFRaw<ST>::decode(cr[u], sc);
                     if (!in) cv = {(T)0, (T)0};
-                    if (gm.conj) cv.y = -cv.y;
+                    if (form & kConj) cv.y = -cv.y;
                     if (PO) cv = cmul(cv, phasor<T>(gm, txs[u] - h, tys[u] - h, a.cf.O));
                     for (int p = 0; p < NPOL; ++p) cmac_conj(sum[p], cv, gv[u][p]);
                 }
@@ -302,7 +328,7 @@ __global__ __launch_bounds__(256) void k_degrid_small(DegridArgs a) {
             sum[p].x += __shfl_xor(sum[p].x, off);
             sum[p].y += __shfl_xor(sum[p].y, off);
         }
-    if (live && sub == 0) store_group<T, NPOL>(a, g, sum);
+    if (live && sub == 0) store_group<T, NPOL>(a, g, form, sum);
 }
 
 template <typename T, int ST, int NPOL>

@@ -1,9 +1,9 @@
-// Gridding G (Eq. IMAGE-MOD) on gfx950 (no MFMA: the work is a scatter /
-// gather, not a dense contraction), over a binning plan:
+// Gridding G (Eq. IMAGE-MOD) on gfx950, over a binning plan:
 //   presum   for every group of samples that share plane, kernel and
 //            footprint, A_g = sum W V (exact regrouping of the sum; FP32 or
 //            FP64), together with the class counters and FP64 sum of weights;
-//   grid     one workgroup per chunk of the (tile, group) pairs of a 32 x 32
+//   grid     (FP64 here, FP32 in k_tile32.hip)
+//            one workgroup per chunk of the (tile, group) pairs of a 32 x 32
 //            cell tile.  Each thread owns four cells of the tile and
 //            accumulates Ct(o, t) phi(t) A_g over every group covering them in
 //            registers; the tile is written once at the end, with plain loads
@@ -23,6 +23,7 @@
 #include "lr_internal.h"
 #include "lr_launch.h"
 #include "k_common.h"
+#include "k_tile.h"
 
 namespace lr {
 __global__ void k_zero(uint4 *p, int64_t n16, uint8_t *tail, int ntail) {
@@ -387,42 +388,11 @@ static void col_shape(int64_t n_pairs, int64_t L, int64_t &ncb, int32_t &n_block
 // tile after the chunks, which writes zeros when the tile has no pairs, so
 // the kernel writes every cell of the grid once (shared tiles are cleared
 // by the call's set-up kernel before it).
-struct TileArgs {
-    const GroupMeta *groups;
-    const int32_t *tp_group, *chunk_start, *chunk_tile, *chunk_excl, *chunk_order, *tile_state;
-    const void *A;
-    void *grid;
-    CFView cf;
-    int32_t nx, ny, ntx, nty;
-    int64_t pol_stride;   // nx * ny
-    int32_t n_chunks;
-    int32_t set;          // GRID_SET: exclusive chunks overwrite their whole tile
-    uint32_t mix;         // Mueller pass: bit q * NPOL + p adds pol q's sum into slot p (0: none)
-};
-
-// Thread t of a 256-thread workgroup clears column t % 32 of tile `tile`.
-template <typename T, int NPOL>
-__device__ __forceinline__ void clear_tile(int tile, int32_t ntx, int32_t nty, int32_t nx,
-                                           int32_t ny, int64_t pol_stride, cpx<T> *grid) {
-    const int tx = tile % ntx;
-    const int rest = tile / ntx;
-    const int ty = rest % nty;
-    const int P = rest / nty;
-    const int x = tx * kTile + (threadIdx.x & 31);
-    if (x >= nx) return;
-    for (int r = threadIdx.x >> 5; r < kTile; r += blockDim.x >> 5) {
-        const int y = ty * kTile + r;
-        if (y >= ny) break;
-        for (int p = 0; p < NPOL; ++p)
-            grid[((int64_t)P * NPOL + p) * pol_stride + (int64_t)y * nx + x] = {(T)0, (T)0};
-    }
-}
-
 // Per-pair data of a chunk, staged in LDS once per workgroup.
 struct TileItem {
     int64_t cf_off;
     int32_t bx, by;   // footprint origin p - h
-    int32_t S, conj;
+    int32_t S, form;
     float sc;         // 2^-e of the CF plane
     int32_t h;
 };
@@ -484,7 +454,7 @@ __global__ __launch_bounds__(256) void k_grid_tile(TileArgs a) {
             ti.bx = gm.pu - h;
             ti.by = gm.pv - h;
             ti.S = 2 * h + 1;
-            ti.conj = gm.conj;
+            ti.form = gm.form;
             ti.sc = a.cf.scale[(int64_t)gm.fg * a.cf.n_w + gm.k];
             ti.h = h;
             items[t] = ti;
@@ -502,6 +472,7 @@ __global__ __launch_bounds__(256) void k_grid_tile(TileArgs a) {
                             v.x += in[q].x;
                             v.y += in[q].y;
                         }
+                    if (negated(a.cf, gm.form)) v = {-v.x, -v.y};
                     avs[t * NPOL + p] = v;
                 }
             }
@@ -559,16 +530,22 @@ __global__ __launch_bounds__(256) void k_grid_tile(TileArgs a) {
                 rs[b] = r;
                 const bool cin = (unsigned)dx < (unsigned)S;
                 const unsigned SS = (unsigned)(S * S);
+                // tap (r + j, dx) of the footprint, at the mirrored place of the
+                // sub-kernel on flipped axes
+                const int form = uni(ti.form);
+                const int su = form & kFlipU ? -1 : 1, sv = form & kFlipV ? -S : S;
+                const int k0 = (form & kFlipU ? S - 1 : 0) + (form & kFlipV ? (S - 1) * S : 0);
                 int off = __mul24(r, S) + dx;  // element offset of the lane's first row
-                for (int j = 0; j < 4; ++j, off += S) {
+                int at = __mul24(r, sv) + (__mul24(dx, su) + k0);
+                for (int j = 0; j < 4; ++j, off += S, at += sv) {
                     ok[b][j] = cin && (unsigned)off < SS;
-                    if (ok[b][j]) cv[b][j] = *(const Raw *)(base + (uint32_t)off * (uint32_t)E);
+                    if (ok[b][j]) cv[b][j] = *(const Raw *)(base + (uint32_t)at * (uint32_t)E);
                 }
             }
             for (int b = 0; b < B; ++b) {
                 if (idx[b] < 0) continue;
                 const int t = idx[b];
-                const bool cj = uni(items[t].conj) != 0;
+                const bool cj = (uni(items[t].form) & kConj) != 0;
                 cpx<T> av[NPOL];
                 for (int p = 0; p < NPOL; ++p) av[p] = avs[t * NPOL + p];
                 for (int j = 0; j < 4; ++j) {
@@ -980,12 +957,8 @@ hipError_t launch_grid(const lr_plan *P, const CFView &cf, const void *A, void *
     bool po = P->po != 0;
     bool psf = mode == GRID_PSF;
     det = det && !psf;
-    switch (precision) {
-        case LR_F64: return grid_np<double, LR_F64>(ta, nc, npol, po, psf, det, s);
-        case LR_F32: return grid_np<float, LR_F32>(ta, nc, npol, po, psf, det, s);
-        case LR_F32_CF16: return grid_np<float, LR_F32_CF16>(ta, nc, npol, po, psf, det, s);
-        default: return grid_np<float, LR_F32_CFBF16>(ta, nc, npol, po, psf, det, s);
-    }
+    if (precision == LR_F64) return grid_np<double, LR_F64>(ta, nc, npol, po, psf, det, s);
+    return launch_grid_tile32(ta, nc, precision, npol, po, psf, det, s);
 }
 
 template <typename T, int NPOL>

@@ -230,12 +230,12 @@ __global__ __launch_bounds__(256) void k_group_meta(
         const int64_t S = 2 * h + 1;
         const int64_t no = g.O + 1;
         gm.cf_off = cf.plane_off[(int64_t)ch.fg * g.n_w + m.k] +
-                    ((int64_t)(m.ov + (g.O >> 1)) * no + (m.ou + (g.O >> 1))) * S * S;
+                    ((int64_t)((g.O >> 1) - abs(m.ov)) * no + ((g.O >> 1) - abs(m.ou))) * S * S;
         gm.cell = ((int64_t)ch.plane * g.npol) * (int64_t)g.ny * g.nx + (int64_t)m.pv * g.nx + m.pu;
         gm.pu = m.pu;
         gm.pv = m.pv;
         gm.k = m.k;
-        gm.conj = m.conj;
+        gm.form = (m.conj ? kConj : 0) | (m.ou > 0 ? kFlipU : 0) | (m.ov > 0 ? kFlipV : 0);
         gm.ou = m.ou;
         gm.ov = m.ov;
         gm.plane = ch.plane;
@@ -339,7 +339,7 @@ __global__ __launch_bounds__(256) void k_tile_chunks(const int32_t *tile_tp, con
 // two 8-bit digits); the chunk ids ride along.  Slots past the chunks sort
 // last.
 constexpr int kCostBits = 16;
-static_assert(kChunkCells <= 2 << (kCostBits - 1), "chunk cost exceeds its sort digits");
+static_assert(kChunkCells >> 1 < 1 << kCostBits, "chunk cost exceeds its sort digits");
 
 __global__ __launch_bounds__(256) void k_chunk_cost(const int32_t *chunk_start,
                                                     const int32_t *chunk_tile,
@@ -365,7 +365,7 @@ __global__ __launch_bounds__(256) void k_chunk_cost(const int32_t *chunk_start,
     }
     for (int off = 32; off > 0; off >>= 1) w += __shfl_xor(w, off);
     if (lane == 0) {
-        key[c] = min((uint32_t)(kChunkCells - w) >> 1, (1u << kCostBits) - 1);
+        key[c] = (uint32_t)(kChunkCells - (int)w) >> 1;
         id[c] = (int32_t)c;
     }
 }

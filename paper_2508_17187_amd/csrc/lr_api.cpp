@@ -232,6 +232,7 @@ CFView view_of(const lr_cf *cf) {
     // kernel: its imaginary parts are rounding noise
     const uint32_t t = cf->spec.terms;
     v.real = !(t & LR_TERM_A) && (!(t & LR_TERM_W) || cf->spec.n_w == 1) ? 1 : 0;
+    v.odd = 0;
     v.h0 = cf->h[0];
     v.off0 = cf->plane_off[0];
     return v;
@@ -242,6 +243,7 @@ CFView view_kind(const lr_cf *cf, int32_t kind) {
     CFView v = view_of(cf);
     v.table = (const char *)cf->d_table + (size_t)kind * cf->kind_elems * cf->elem_bytes;
     v.scale = cf->d_scale + (size_t)kind * cf->spec.n_fg * cf->spec.n_w;
+    v.odd = kind == 3 || kind == 4 ? 1 : 0;      // E_X d, E_Y d: d is odd in l and in m
     return v;
 }
 

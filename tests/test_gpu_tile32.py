@@ -1,0 +1,77 @@
+"""GPU: the FP32 tile gridder: tiles of one to several chunks of groups,
+every storage form and number of correlations, supports below and above a
+tile, footprints mirrored on each axis, edge tiles of a ragged grid; and
+group sums that are not finite, which must stay inside their footprints."""
+
+import numpy as np
+import pytest
+
+import oracle
+import synth
+from oracle.cfbuild import TERM_A, TERM_PS, TERM_W
+from oracle.native import Problem
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+if not torch.cuda.is_available():
+    pytest.skip("no GPU", allow_module_level=True)
+
+from paper_2508_17187_amd import lr  # noqa: E402
+from paper_2508_17187_amd import workload as W  # noqa: E402
+
+TOL = {"f32": 1e-5, "f16cf": 3e-3, "bf16cf": 2e-2}      # the forms' parity bounds
+
+
+def make(npol, h_max, n_time, pointing=False, nx=118, ny=90):
+    return synth.tiny_workload(n_ant=7, n_time=n_time, nchan=2, npol=npol, nx=nx, ny=ny,
+                               cell_arcsec=5.0, diameter_m=4000.0, oversample=6, n_w=4, h_min=2,
+                               h_max=h_max, terms=TERM_PS | TERM_W | TERM_A, fg_hz=[3e9],
+                               pointing_sigma=3e-5 if pointing else 0.0, cfg_id=280)
+
+
+@pytest.mark.parametrize("form", list(TOL))
+@pytest.mark.parametrize("npol", [1, 2, 4])
+@pytest.mark.parametrize("h_max,n_time", [(3, 2), (9, 40), (17, 200), (33, 30)])
+def test_grid_matches_the_oracle(form, npol, h_max, n_time):
+    prec = lr.PRECISIONS[form]
+    wl = make(npol, h_max, n_time)
+    cf = W.build_cf(wl, prec)
+    v = W.device_vis(wl, prec)
+    v.plan = lr.Plan(cf, v)
+    ref = Problem.from_workload(wl, oracle.build_cf(wl.grid, wl.cf)).grid(wl.vis, wl.weight)
+    g = W.empty_grid(wl, prec)
+    for call in (lr.lr_grid, lr.lr_grid_overwrite):
+        call(cf, v, prec, g)
+        assert np.linalg.norm(g.cpu().numpy() - ref) <= TOL[form] * np.linalg.norm(ref)
+
+
+@pytest.mark.parametrize("form", list(TOL))
+@pytest.mark.parametrize("npol", [1, 4])
+@pytest.mark.parametrize("pointing", [False, True])
+@pytest.mark.parametrize("bad", [float("inf"), float("nan"), -3e38])
+def test_sums_that_are_not_finite_stay_in_their_footprint(form, npol, pointing, bad):
+    prec = lr.PRECISIONS[form]
+    wl = make(npol, 9, 20, pointing)
+    cf = W.build_cf(wl, prec)
+    v = W.device_vis(wl, prec)
+    wt = v.weight.clone()
+    pm = lr.lr_debug_map(cf, v).cpu().numpy()
+    row = int(np.nonzero(pm[:, 0, 6])[0][5])
+    wt[row, 0] = 0
+    without = W.empty_grid(wl, prec)
+    lr.lr_grid(cf, v.with_(weight=wt), prec, without)
+    vis = v.vis.clone()
+    vis[row, 0] = complex(bad, 0.0)
+    wt[row, 0] = 2.0 if bad == bad and abs(bad) != float("inf") else 1.0
+    with_ = W.empty_grid(wl, prec)
+    lr.lr_grid(cf, v.with_(vis=vis, weight=wt), prec, with_)
+    pu, pv, k = pm[row, 0, 0], pm[row, 0, 1], pm[row, 0, 4]
+    h = int(oracle.build_cf(wl.grid, wl.cf).h[k])
+    inside = torch.zeros(without.shape[-2:], dtype=torch.bool, device="cuda")
+    inside[pv - h:pv + h + 1, pu - h:pu + h + 1] = True
+    a, b = with_[0], without[0]
+    assert torch.isfinite(torch.view_as_real(a[:, ~inside])).all()
+    # the other samples' sums, to the rounding of another order of additions
+    assert (a - b)[:, ~inside].abs().max() <= 1e-5 * b.abs().max()
+    assert not torch.isfinite(torch.view_as_real(a[:, inside])).all()
