@@ -93,7 +93,7 @@ hipError_t launch_debug_map(int64_t nrow, int32_t nchan, const double *uvw,
 
 // ---------------------------------------------------------------------------
 // Sort keys.  Fields from most to least significant: plane, A-term group,
-// w-plane, conj, p_v, p_u, [baseline, channel when a pointing phasor is
+// w-plane, block of pixels (v, u), conj, p_v, p_u in the block, [baseline, channel when a pointing phasor is
 // applied], o_v, o_u.  Keys of dropped or skipped pairs are all ones, which
 // no kept pair's 63 bits reach.
 constexpr uint64_t kDropKey = ~0ull;
@@ -123,9 +123,12 @@ __global__ __launch_bounds__(256) void k_plan_keys(uint32_t n_pairs, uint32_t nc
             put(k128, (uint32_t)ch.plane, kl.b_plane);
             put(k128, (uint32_t)ch.fg, kl.b_fg);
             put(k128, (uint32_t)m.k, kl.b_k);
+            const uint32_t low = (1u << kl.b_blk) - 1;
+            put(k128, (uint32_t)m.pv >> kl.b_blk, kl.b_pv - kl.b_blk);
+            put(k128, (uint32_t)m.pu >> kl.b_blk, kl.b_pu - kl.b_blk);
             put(k128, (uint32_t)m.conj, kl.b_conj);
-            put(k128, (uint32_t)m.pv, kl.b_pv);
-            put(k128, (uint32_t)m.pu, kl.b_pu);
+            put(k128, (uint32_t)m.pv & low, kl.b_blk);
+            put(k128, (uint32_t)m.pu & low, kl.b_blk);
             if (kl.b_bl) put(k128, (uint32_t)(ant1[r] * nant + ant2[r]), kl.b_bl);
             if (kl.b_ch) put(k128, c, kl.b_ch);
             put(k128, (uint32_t)(m.ov + (g.O >> 1)), kl.b_o);
@@ -166,8 +169,10 @@ struct GroupHead {
             f >>= bits;
             return v;
         };
-        const int pu = field(kl.b_pu), pv = field(kl.b_pv);
+        int pu = field(kl.b_blk), pv = field(kl.b_blk);
         f >>= kl.b_conj;
+        pu |= field(kl.b_pu - kl.b_blk) << kl.b_blk;
+        pv |= field(kl.b_pv - kl.b_blk) << kl.b_blk;
         const int k = field(kl.b_k);
         int tx0, tx1, ty0, ty1;
         tile_span(pu, pv, h[k], tx0, tx1, ty0, ty1);

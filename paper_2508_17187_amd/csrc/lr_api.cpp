@@ -371,6 +371,12 @@ KeyLayout key_layout(const lr_cf *cf, const lr_vis *v, bool po, int32_t &merged)
     k.b_bl = po ? bitwidth((int64_t)v->nant * v->nant - 1) : 0;
     k.b_ch = po ? bitwidth(v->nchan - 1) : 0;
     k.b_o = bitwidth(cf->spec.oversample - 1);
+    // groups of one kernel plane come in blocks of pixels, whose footprints
+    // share most of their cells (in the L2 while the degridder gathers); the
+    // separable gridder needs a tile's pairs by pixel row instead
+    const uint32_t t = cf->spec.terms;
+    const bool rows = cf->spec.n_w == 1 && !(t & LR_TERM_A);
+    k.b_blk = rows ? 0 : std::min(kBlockBits, std::min(k.b_pv, k.b_pu));
     int total = k.b_plane + k.b_fg + k.b_k + k.b_conj + k.b_pv + k.b_pu + k.b_bl + k.b_ch + 2 * k.b_o;
     if (total <= 63) {
         k.shift = 0;

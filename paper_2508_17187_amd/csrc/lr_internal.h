@@ -39,6 +39,7 @@ constexpr int32_t kGroupFlags = kSingleRun | kSingleton;
 constexpr int32_t kConj = 1;        // conjugated (w < 0)
 constexpr int32_t kFlipU = 2;       // o_u > 0: columns backwards
 constexpr int32_t kFlipV = 4;       // o_v > 0: rows backwards
+constexpr int32_t kBlockBits = 4;   // blocks of 16 x 16 pixels in the group order
 constexpr int kSepPart = 4096;     // most (tile, group) pairs per workgroup of the separable gridder
 constexpr int kSepPartMin = 64;    // shortest part when few tiles hold all pairs
 constexpr int kSepFill = 1024;     // parts that fill the chip

@@ -10,6 +10,7 @@ namespace lr {
 // ---- plan (k_plan.hip) -------------------------------------------------------
 struct KeyLayout {
     int32_t b_plane, b_fg, b_k, b_conj, b_pv, b_pu, b_bl, b_ch, b_o;
+    int32_t b_blk;     // pixel bits below the block of 2^b_blk x 2^b_blk pixels
     int32_t shift;     // right shift applied to the full key
     int32_t end_bit;   // significant bits of the final key
 };
