@@ -1111,12 +1111,12 @@ lr_status lr_degrid(const lr_cf *cf, lr_vis *vis, lr_precision precision, const 
     hipError_t e = hipSuccess;
     if (cf->n_kind == 1) {
         e = launch_degrid(P, view_of(cf), grid, Vg, precision, vis->npol, cf->grid.nx,
-                          cf->grid.ny, h_max_of(cf), 0u, false, s);
+                          cf->grid.ny, cf->grid.nplane, h_max_of(cf), 0u, false, s);
     } else {
         // one pass per Mueller kind, each adding its elements' gathers
         for (int32_t kind = 0; kind < cf->n_kind && e == hipSuccess; ++kind)
             e = launch_degrid(P, view_kind(cf, kind), grid, Vg, precision, vis->npol,
-                              cf->grid.nx, cf->grid.ny, h_max_of(cf),
+                              cf->grid.nx, cf->grid.ny, cf->grid.nplane, h_max_of(cf),
                               kind_mask(cf, kind, vis->npol), kind > 0, s);
     }
     prof.end();
