@@ -106,8 +106,8 @@ hipError_t launch_grid_setup(const lr_plan *P, void *A, size_t a_bytes, double *
 // mix (Mueller passes; 0 = none): bit q * npol + p set when grid pol p's
 // gather adds into correlation q; accum adds to Vg instead of writing it.
 hipError_t launch_degrid(const lr_plan *P, const CFView &cf, const void *grid, void *Vg,
-                         int precision, int32_t npol, int32_t nx, int32_t ny, int32_t h_max,
-                         uint32_t mix, bool accum, hipStream_t s);
+                         int precision, int32_t npol, int32_t nx, int32_t ny, int32_t nplane,
+                         int32_t h_max, uint32_t mix, bool accum, hipStream_t s);
 hipError_t launch_expand(const lr_plan *P, const void *Vg, void *vis, const void *weight,
                          int precision, int32_t npol, hipStream_t s);
 
@@ -127,7 +127,8 @@ hipError_t launch_ps_taper(double c, int use_ps, int32_t n, double *out, hipStre
 hipError_t launch_pb_image(const lr_cf *cf, const double *w, double *out, hipStream_t s);
 
 // ---- minor cycle (k_hogbom.hip) -------------------------------------------------
-constexpr int kHogbomBlocks = 1024;      // workgroups of the peak search
+constexpr int kHogbomBlocks = 512;       // most workgroups of a subtraction and search
+constexpr int kHogbomThreads = 512;
 size_t hogbom_work_bytes(int32_t nx, int32_t ny);
 hipError_t launch_hogbom(void *res, const void *psf, void *model, int32_t nx, int32_t ny,
                          int precision, double gain, double threshold, int32_t niter,

@@ -101,3 +101,34 @@ def test_ragged_image_and_ties():
     m, r, it = run(dirty, psf, torch.float64, 0.3, 0.05, 60)
     assert it == it_ref
     assert np.array_equal(m, m_ref) and np.array_equal(r, r_ref)
+
+
+@pytest.mark.parametrize("ny,nx", [(1, 1), (3, 2), (5, 3), (37, 50), (64, 1023), (600, 1001),
+                                   (1500, 1400)])
+@pytest.mark.parametrize("niter", [1, 2, 9])
+def test_sizes_around_the_quads_and_workgroups(ny, nx, niter):
+    """Rows that are not whole quads of pixels, images smaller than a
+    workgroup and larger than one pass of all of them, peaks near the edges
+    (the PSF partly outside on each side): identical to the oracle in FP64."""
+    rng = np.random.default_rng(ny * nx)
+    psf = rng.normal(0, 0.1, (ny, nx))
+    psf[ny // 2, nx // 2] = 1.0
+    dirty = rng.normal(0, 0.1, (ny, nx))
+    for y, x, v in ((0, 0, 3.0), (ny - 1, nx - 1, -2.9), (ny // 2, nx - 1, 2.8)):
+        dirty[y, x] = v
+    m_ref, r_ref, it_ref = hogbom(dirty, psf, 0.2, 0.0, niter)
+    m, r, it = run(dirty, psf, torch.float64, 0.2, 0.0, niter)
+    assert it == it_ref
+    assert np.array_equal(m, m_ref) and np.array_equal(r, r_ref)
+
+
+def test_no_finite_pixel_and_reuse_of_the_workspace():
+    res = torch.full((40, 40), float("nan"), dtype=torch.float64, device=DEV)
+    psf, model = torch.ones_like(res), torch.zeros_like(res)
+    work = torch.full((lr.lib().lr_hogbom_work_bytes(40, 40),), 0x7F, dtype=torch.uint8, device=DEV)
+    assert lr.lr_hogbom(psf, res, model, 0.1, 0.0, 5, work=work) == 0
+    assert not model.any()
+    res = torch.zeros_like(res)
+    res[7, 9] = 1.0
+    assert lr.lr_hogbom(psf, res, model, 0.1, 0.5, 3, work=work) == 3
+    assert model.count_nonzero() == 1 and model[7, 9] != 0
