@@ -411,18 +411,21 @@ __global__ void k_single_gaps(const int32_t *order, const int32_t *gidx, int64_t
 
 // One-member groups (bit 1 of single[g]; the presum stores their sums, which
 // never need a cleared start) and the list of the other groups, which the
-// presum may add to with atomics (any order).  A wavefront takes 1024
-// groups, so that the list's end moves once per 1024.
+// presum may add to with atomics (any order).  A wavefront takes up to 1024
+// groups, so that the list's end moves once per 1024 (the end is one word, and
+// requests to it go one after another), and fewer when there are few.
 constexpr int kKindRounds = 16;
 
 __global__ __launch_bounds__(256) void k_group_kinds(const int32_t *group_start, int64_t n_groups,
-                                                     int32_t *single, int32_t *multi,
-                                                     PlanCounts *pc) {
+                                                     int32_t rounds, int32_t *single,
+                                                     int32_t *multi, PlanCounts *pc) {
     const int lane = threadIdx.x & 63;
-    const int64_t g0 = (((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6) * (64 * kKindRounds);
+    const int64_t g0 = (((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6) * (64 * rounds);
     uint64_t many[kKindRounds];
     int total = 0;
     for (int r = 0; r < kKindRounds; ++r) {
+        many[r] = 0;
+        if (r >= rounds) continue;
         const int64_t g = g0 + r * 64 + lane;
         const bool in = g < n_groups;
         const bool one = in && group_start[g + 1] - group_start[g] == 1;
@@ -530,14 +533,21 @@ __global__ void k_pair_group(const int32_t *order, const int32_t *gidx, const in
 __global__ void k_row_period(const double *uvw, int64_t nrow, int32_t rmax, int32_t *best) {
     int32_t r = blockIdx.x * blockDim.x + threadIdx.x + 1;
     if (r > rmax) return;
-    int64_t nchk = nrow - r < 64 ? nrow - r : 64;
+    const int nchk = (int)(nrow - r < 64 ? nrow - r : 64);
     if (nchk < 4) return;
-    for (int64_t i = 0; i < nchk; ++i) {
-        double a0 = uvw[3 * i], a1 = uvw[3 * i + 1], a2 = uvw[3 * i + 2];
-        double b0 = uvw[3 * (i + r)], b1 = uvw[3 * (i + r) + 1], b2 = uvw[3 * (i + r) + 2];
-        double d = fabs(a0 - b0) + fabs(a1 - b1) + fabs(a2 - b2);
-        double s = fabs(a0) + fabs(a1) + fabs(a2);
-        if (!(d <= 1e-2 * s + 1e-3)) return;
+    // eight rows' loads in flight together: the true period's thread checks all
+    // 64, and row by row that was 16 us of every plan
+    for (int i0 = 0; i0 < nchk; i0 += 8) {
+        bool same = true;
+        for (int k = 0; k < 8; ++k) {
+            const int64_t i = min(i0 + k, nchk - 1);
+            const double a0 = uvw[3 * i], a1 = uvw[3 * i + 1], a2 = uvw[3 * i + 2];
+            const double b0 = uvw[3 * (i + r)], b1 = uvw[3 * (i + r) + 1], b2 = uvw[3 * (i + r) + 2];
+            const double d = fabs(a0 - b0) + fabs(a1 - b1) + fabs(a2 - b2);
+            const double s = fabs(a0) + fabs(a1) + fabs(a2);
+            same = same && d <= 1e-2 * s + 1e-3;
+        }
+        if (!same) return;
     }
     atomicMin(best, r);
 }
@@ -811,8 +821,9 @@ hipError_t build_plan_device(lr_plan *P, char *buf, const PlanLayout &L, const d
         hipLaunchKernelGGL(k_single_init, dim3(blocks(ng, 256)), dim3(256), 0, s, single, ng, 1);
         hipLaunchKernelGGL(k_single_gaps, dim3(blocks(nk, 256)), dim3(256), 0, s, order, gidx,
                            nk, P->period, single);
-        hipLaunchKernelGGL(k_group_kinds, dim3(blocks(ng, 256 * kKindRounds)), dim3(256), 0, s,
-                           P->group_start, ng, single, P->multi, pc);
+        const int32_t rounds = (int32_t)std::max<int64_t>(1, std::min<int64_t>(kKindRounds, ng >> 16));
+        hipLaunchKernelGGL(k_group_kinds, dim3(blocks(ng, 256 * rounds)), dim3(256), 0, s,
+                           P->group_start, ng, rounds, single, P->multi, pc);
     }
     hipLaunchKernelGGL(k_pair_group, dim3(blocks(n, 256)), dim3(256), 0, s, order, gidx,
                        (const int32_t *)single, nk, n, P->pair_group);
