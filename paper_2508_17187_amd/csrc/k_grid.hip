@@ -411,11 +411,11 @@ __global__ __launch_bounds__(256) void k_grid_tile(TileArgs a) {
     __shared__ TileItem items[kChunkMax];
     __shared__ cpx<T> avs[kChunkMax * NPOL];
     __shared__ GroupMeta gms[PO ? kChunkMax : 1];
+    __shared__ cpx<T> rows[PSF ? 1 : 4][PSF ? 1 : 64];   // two rows of a band, one pol
     // workgroups take the chunks in the plan's order (largest first, or tile
     // order without chunk_order); those after the chunks (GRID_SET) clear
     // the tiles without pairs
-    const int c0 = a.chunk_order && (int)blockIdx.x < a.n_chunks ? a.chunk_order[blockIdx.x]
-                                                                  : (int)blockIdx.x;
+    const int c0 = (int)blockIdx.x < a.n_chunks ? chunk_of(a, (int)blockIdx.x) : (int)blockIdx.x;
     if (!PSF && c0 >= a.n_chunks) {      // GRID_SET: tiles without pairs
         const int tile = c0 - a.n_chunks;
         if (a.tile_state[tile] == 0)
@@ -577,6 +577,27 @@ __global__ __launch_bounds__(256) void k_grid_tile(TileArgs a) {
     }
     T *grid = (T *)a.grid;
     const bool set = excl && a.set;
+    if (!PSF && !excl) {
+        // A tile several chunks share takes device-wide atomics, which leave
+        // the L2 as one request per 64 bytes and instruction: through LDS a
+        // row's 64 values go out in one instruction, eight full requests,
+        // where lanes adding their own cells made sixteen half-empty ones.
+        const int wv = threadIdx.x >> 6, w = 2 * min(kTile, a.nx - tx * kTile);
+        for (int j = 0; j < 4; ++j)
+            for (int p = 0; p < NPOL; ++p) {
+                rows[wv][lane] = acc[j][p];
+                __builtin_amdgcn_wave_barrier();
+                for (int r = 0; r < 2; ++r) {
+                    const int y = band0 + 4 * r + j;
+                    const T v = ((const T *)rows[wv])[64 * r + lane];
+                    if (v != (T)0 && lane < w && y < a.ny)
+                        atomicAdd(grid + 2 * (((int64_t)P * NPOL + p) * a.pol_stride +
+                                              (int64_t)y * a.nx + tx * kTile) + lane, v);
+                }
+                __builtin_amdgcn_wave_barrier();
+            }
+        return;
+    }
     for (int j = 0; j < 4; ++j) {
         const int y = yb + j;
         if (set) {
@@ -601,12 +622,9 @@ __global__ __launch_bounds__(256) void k_grid_tile(TileArgs a) {
             } else if (set) {
                 q[0] = acc[j][p].x;
                 q[1] = acc[j][p].y;
-            } else if (excl) {
+            } else {
                 q[0] += acc[j][p].x;
                 q[1] += acc[j][p].y;
-            } else {
-                atomicAdd(q, acc[j][p].x);
-                atomicAdd(q + 1, acc[j][p].y);
             }
         }
     }
@@ -953,7 +971,7 @@ hipError_t launch_grid(const lr_plan *P, const CFView &cf, const void *A, void *
     TileArgs ta{P->groups, P->tp_group, P->chunk_start, P->chunk_tile, P->chunk_excl,
                 P->chunk_order, P->tile_state, A, grid, cf, nx, ny, (nx + kTile - 1) / kTile,
                 (ny + kTile - 1) / kTile, (int64_t)nx * ny, (int32_t)P->n_chunks,
-                set ? 1 : 0, mix};
+                set ? 1 : 0, P->by_plane ? kChunkRun : 0, mix};
     bool po = P->po != 0;
     bool psf = mode == GRID_PSF;
     det = det && !psf;

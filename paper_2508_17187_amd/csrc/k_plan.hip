@@ -691,6 +691,7 @@ hipError_t build_plan_device(lr_plan *P, char *buf, const PlanLayout &L, const d
     P->chunk_tile = (int32_t *)(buf + L.chunk_tile);
     P->chunk_excl = (int32_t *)(buf + L.chunk_excl);
     P->chunk_order = nullptr;
+    P->by_plane = 0;
     P->tile_state = (int32_t *)(buf + L.tile_state);
     P->n_tiles = nt;
     P->shared_tiles = (int32_t *)(buf + L.shared_tiles);
@@ -807,6 +808,7 @@ hipError_t build_plan_device(lr_plan *P, char *buf, const PlanLayout &L, const d
                                (uint32_t)planes - 1, slots, pc, tk_a, vals_a);
         }
         P->chunk_order = (int32_t *)(buf + L.chunk_order);
+        P->by_plane = lpt ? 0 : 1;
         e = rocprim::radix_sort_pairs<SortConfig>(temp, temp_bytes, tk_a, (uint32_t *)scan, vals_a,
                                                   P->chunk_order, (size_t)slots, 0, end_bits, s);
         if (e != hipSuccess) return e;

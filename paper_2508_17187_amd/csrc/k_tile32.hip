@@ -76,8 +76,7 @@ __global__ __launch_bounds__(256, PO ? 2 : 4) void k_grid_tile32(TileArgs a) {
     __shared__ uint16_t lists[4][MAXI + 2 * kBatch];
     __shared__ GroupMeta gms[PO ? MAXI : 1];
     __shared__ cpx<float> rows[PSF ? 1 : 4][PSF ? 1 : 64];   // two rows of a band, one pol
-    const int c0 = a.chunk_order && (int)blockIdx.x < a.n_chunks ? a.chunk_order[blockIdx.x]
-                                                                  : (int)blockIdx.x;
+    const int c0 = (int)blockIdx.x < a.n_chunks ? chunk_of(a, (int)blockIdx.x) : (int)blockIdx.x;
     if (!PSF && c0 >= a.n_chunks) {      // GRID_SET: tiles without pairs
         const int tile = c0 - a.n_chunks;
         if (a.tile_state[tile] == 0)

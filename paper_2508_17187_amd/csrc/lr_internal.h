@@ -176,6 +176,7 @@ struct lr_plan {
     int32_t *chunk_order;      // [n_chunks] launch order: by estimated work, largest
                                // first, for kernel tables the last-level cache holds;
                                // plane by plane for larger ones (null: no chunks)
+    int32_t by_plane;          // chunk_order goes plane by plane
     int32_t *tile_state;       // [n_tiles] 0 no pairs, 1 one exclusive chunk, 2 several chunks
     int64_t n_tiles;           // nplane * nty * ntx
     int32_t *shared_tiles;     // [n_shared] ids of the tiles in state 2
