@@ -3,6 +3,7 @@
 // decomposition of the gridder's work into wavefront tasks.
 #include <string.h>
 
+#include <cstddef>
 #include <cstring>
 
 #include <rocprim/rocprim.hpp>
@@ -186,17 +187,26 @@ __device__ __forceinline__ double airy_power(double x) {
     return b * b;
 }
 
-// Sums of a workgroup's threads added to *out, one request per workgroup.
-__device__ __forceinline__ void block_add(unsigned long long v, unsigned long long *out) {
-    __shared__ unsigned long long part[4];
-    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
-    if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = v;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        v = part[0] + part[1] + part[2] + part[3];
-        if (v) atomicAdd(out, v);
+// Sums of a workgroup's threads added to out[0] and out[1], one request per
+// workgroup (two lanes of one instruction; requests to one word go one after
+// another).
+__device__ __forceinline__ void block_add2(unsigned long long u, unsigned long long v,
+                                           unsigned long long *out) {
+    __shared__ unsigned long long part[4][2];
+    for (int off = 32; off > 0; off >>= 1) {
+        u += __shfl_xor(u, off);
+        v += __shfl_xor(v, off);
+    }
+    if ((threadIdx.x & 63) == 0) {
+        part[threadIdx.x >> 6][0] = u;
+        part[threadIdx.x >> 6][1] = v;
     }
     __syncthreads();
+    if (threadIdx.x < 2) {
+        const int i = threadIdx.x;
+        const unsigned long long s = part[0][i] + part[1][i] + part[2][i] + part[3][i];
+        if (s) atomicAdd(out + i, s);
+    }
 }
 
 // Groups from the scan over the sorted pairs: the group of every pair, the
@@ -278,8 +288,8 @@ __global__ __launch_bounds__(256) void k_group_meta(
             }
         tiles += (unsigned long long)((tx1 - tx0 + 1) * (ty1 - ty0 + 1));
     }
-    block_add(taps, &pc->taps);
-    block_add(tiles, &pc->n_tile_pairs);
+    static_assert(offsetof(PlanCounts, n_tile_pairs) == 8, "taps and n_tile_pairs are added as one");
+    block_add2(taps, tiles, &pc->taps);
 }
 
 // ---- tiles of the gridder ----------------------------------------------------
@@ -569,8 +579,12 @@ __global__ void k_plan_init(PlanCounts *pc, int32_t *tile_state, int32_t *tile_t
 static size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
 // Radix sorts of the build.  Up to this many items the library's merge sort
-// is used, beyond it the one-sweep radix sort.
-constexpr unsigned kMergeSortMost = 1 << 15;
+// is used, beyond it the one-sweep radix sort, whose passes each cost several
+// small launches.  Jobs without a plan, one-sweep from 2^15 / 2^17 / 2^18 items
+// on: 5e4 pairs 396 / 315 / 323 us, 1e5 488 / 416 / 409 us, 2e5 604 / 610 / 564
+// us; 1.3e6 pairs (4e5 tile pairs) 769 / 772 / 765 us, and more at the library's
+// own 2^20 (twenty launches of merges).
+constexpr unsigned kMergeSortMost = 1 << 18;
 using SortConfig = rocprim::radix_sort_config<rocprim::default_config, rocprim::default_config,
                                               rocprim::default_config, kMergeSortMost>;
 

@@ -69,7 +69,7 @@ def check(wl, precision=lr.LR_F64):
 
 
 @pytest.mark.parametrize("n", [1, 2, 63, 64, 65, 127, 128, 129, 1000, 5000, 32767, 32768, 32769,
-                               40000])
+                               40000, 262143, 262144, 262150])
 def test_chunk_edges(n):
     info, kept = check(lattice(n))
     assert info["n_groups"] == len(np.unique(kept[:, :6], axis=0))
