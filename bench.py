@@ -190,9 +190,10 @@ def per_sample_taps(cf, v):
 ELEM = {"f64": 16, "f32": 8, "f16cf": 4, "bf16cf": 4}
 CSRC = os.path.join(ROOT, "paper_2508_17187_amd", "csrc")
 # source file of each timed kernel (with the shared device helpers)
-KERNEL_FILES = {"k_grid_tile": "k_grid.hip", "k_presum_col": "k_grid.hip",
-                "k_expand": "k_grid.hip", "k_grid_sep": "k_sep.hip",
-                "k_degrid": "k_degrid.hip", "k_degrid_small": "k_degrid.hip"}
+KERNEL_FILES = {"k_grid_tile": ("k_grid.hip", "k_tile.h", "k_tile32.hip"),
+                "k_presum_col": ("k_grid.hip",), "k_expand": ("k_grid.hip",),
+                "k_grid_sep": ("k_sep.hip",), "k_degrid": ("k_degrid.hip",),
+                "k_degrid_small": ("k_degrid.hip",), "k_degrid_sep": ("k_degrid.hip",)}
 
 
 def kernel_source_sha(kernel):
@@ -201,7 +202,7 @@ def kernel_source_sha(kernel):
     launch order)."""
     import hashlib
     h = hashlib.sha256()
-    for f in ("k_common.h", "k_plan.hip", KERNEL_FILES[kernel]):
+    for f in ("k_common.h", "k_plan.hip") + KERNEL_FILES[kernel]:
         h.update(open(os.path.join(CSRC, f), "rb").read())
     return h.hexdigest()
 

@@ -207,12 +207,13 @@ lr_status lr_cf_kinds(const lr_cf *cf, int32_t *n_kind, int32_t *kind_of);
 size_t lr_plan_bytes(const lr_cf *cf, const lr_vis *vis, int psf);
 
 /* Map every (row, channel), drop what leaves the grid, sort the rest by
- * (plane, CF plane, w-plane, conj, pixel, offset) and merge samples whose
+ * (plane, CF plane, w-plane, block of pixels, conj, pixel, offset; by pixel
+ * row for single-plane tables without an A term) and merge samples whose
  * kernel and footprint are identical into groups.  The plan depends on uvw,
  * frequencies, channel maps, the CF geometry and (with a pointing phasor)
  * the antenna ids, never on visibilities or weights.  psf != 0 builds the
- * plan for the PSF footprint rule.  Synchronises the stream once (group and
- * task counts come back to the host).  buf must stay alive while the plan
+ * plan for the PSF footprint rule.  Synchronises the stream twice (group
+ * and task counts come back to the host).  buf must stay alive while the plan
  * is used; release the handle with lr_plan_free. */
 lr_status lr_plan_build(const lr_cf *cf, const lr_vis *vis, int psf, void *buf,
                         size_t bytes, lr_stream stream, lr_plan **out);

@@ -411,7 +411,7 @@ __global__ __launch_bounds__(256) void k_grid_tile(TileArgs a) {
     __shared__ TileItem items[kChunkMax];
     __shared__ cpx<T> avs[kChunkMax * NPOL];
     __shared__ GroupMeta gms[PO ? kChunkMax : 1];
-    __shared__ cpx<T> rows[PSF ? 1 : 4][PSF ? 1 : 64];   // two rows of a band, one pol
+    __shared__ cpx<T> rows[4][64];                    // two rows of a band, one pol
     // workgroups take the chunks in the plan's order (largest first, or tile
     // order without chunk_order); those after the chunks (GRID_SET) clear
     // the tiles without pairs
@@ -577,11 +577,15 @@ __global__ __launch_bounds__(256) void k_grid_tile(TileArgs a) {
     }
     T *grid = (T *)a.grid;
     const bool set = excl && a.set;
-    if (!PSF && !excl) {
+    if (!excl) {
         // A tile several chunks share takes device-wide atomics, which leave
         // the L2 as one request per 64 bytes and instruction: through LDS a
         // row's 64 values go out in one instruction, eight full requests,
-        // where lanes adding their own cells made sixteen half-empty ones.
+        // where lanes adding their own cells made sixteen half-empty ones.  The
+        // PSF adds half of each row and half of its conjugate mirror image,
+        // whose cells run backwards (row and column 0 receive nothing, so
+        // their images past the grid are never written; W-projection PSF 507 ->
+        // 346 us).
         const int wv = threadIdx.x >> 6, w = 2 * min(kTile, a.nx - tx * kTile);
         for (int j = 0; j < 4; ++j)
             for (int p = 0; p < NPOL; ++p) {
@@ -590,9 +594,17 @@ __global__ __launch_bounds__(256) void k_grid_tile(TileArgs a) {
                 for (int r = 0; r < 2; ++r) {
                     const int y = band0 + 4 * r + j;
                     const T v = ((const T *)rows[wv])[64 * r + lane];
+                    T *pol = grid + 2 * (((int64_t)P * NPOL + p) * a.pol_stride);
                     if (v != (T)0 && lane < w && y < a.ny)
-                        atomicAdd(grid + 2 * (((int64_t)P * NPOL + p) * a.pol_stride +
-                                              (int64_t)y * a.nx + tx * kTile) + lane, v);
+                        atomicAdd(pol + 2 * ((int64_t)y * a.nx + tx * kTile) + lane,
+                                  PSF ? (T)0.5 * v : v);
+                    if (PSF) {
+                        const int c = kTile - 1 - (lane >> 1);        // its cell in the row
+                        const T u = ((const T *)rows[wv])[64 * r + 2 * c + (lane & 1)];
+                        if (u != (T)0 && 2 * c < w && y < a.ny)
+                            atomicAdd(pol + 2 * ((int64_t)(a.ny - y) * a.nx + a.nx - tx * kTile - c) +
+                                          (lane & 1), lane & 1 ? -(T)0.5 * u : (T)0.5 * u);
+                    }
                 }
                 __builtin_amdgcn_wave_barrier();
             }
@@ -613,13 +625,7 @@ __global__ __launch_bounds__(256) void k_grid_tile(TileArgs a) {
         for (int p = 0; p < NPOL; ++p) {
             const int64_t base = ((int64_t)P * NPOL + p) * a.pol_stride;
             T *q = grid + 2 * (base + (int64_t)y * a.nx + x);
-            if (PSF) {
-                T *m = grid + 2 * (base + (int64_t)(a.ny - y) * a.nx + (a.nx - x));
-                atomicAdd(q, (T)0.5 * acc[j][p].x);
-                atomicAdd(q + 1, (T)0.5 * acc[j][p].y);
-                atomicAdd(m, (T)0.5 * acc[j][p].x);
-                atomicAdd(m + 1, -(T)0.5 * acc[j][p].y);
-            } else if (set) {
+            if (set) {
                 q[0] = acc[j][p].x;
                 q[1] = acc[j][p].y;
             } else {

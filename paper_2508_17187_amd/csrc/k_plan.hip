@@ -728,7 +728,11 @@ hipError_t build_plan_device(lr_plan *P, char *buf, const PlanLayout &L, const d
     // The host waits twice: for the numbers of groups and tile pairs, which
     // size the second half's launches, and at the end for what the calls on
     // the plan launch by.  (One wait per count and a launch per small pass
-    // had left the GPU idle for a third of a small build.)
+    // had left the GPU idle for a third of a small build: a degridding job of
+    // 1.6e4 pairs without a plan took 808 us, now 238 us, of which the build
+    // is about 190; a gridding job of 1.3e6 pairs 2340 us, now 750 us.)  What
+    // is left of a small build is the latency of some thirty launches, of a
+    // large one the radix sorts' passes.
     hipLaunchKernelGGL(k_plan_init, dim3(blocks(nt + 1, 256)), dim3(256), 0, s, pc,
                        P->tile_state, P->tile_tp, nt);
     if (n == 0) return hipGetLastError();

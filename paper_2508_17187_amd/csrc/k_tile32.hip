@@ -75,7 +75,7 @@ __global__ __launch_bounds__(256, PO ? 2 : 4) void k_grid_tile32(TileArgs a) {
     __shared__ float avs[(MAXI + 1) * NA];
     __shared__ uint16_t lists[4][MAXI + 2 * kBatch];
     __shared__ GroupMeta gms[PO ? MAXI : 1];
-    __shared__ cpx<float> rows[PSF ? 1 : 4][PSF ? 1 : 64];   // two rows of a band, one pol
+    __shared__ cpx<float> rows[4][64];                // two rows of a band, one pol
     const int c0 = (int)blockIdx.x < a.n_chunks ? chunk_of(a, (int)blockIdx.x) : (int)blockIdx.x;
     if (!PSF && c0 >= a.n_chunks) {      // GRID_SET: tiles without pairs
         const int tile = c0 - a.n_chunks;
@@ -302,12 +302,15 @@ __global__ __launch_bounds__(256, PO ? 2 : 4) void k_grid_tile32(TileArgs a) {
     }
     float *grid = (float *)a.grid;
     const bool set = excl && a.set;
-    if (!PSF && !excl) {
+    if (!excl) {
         // A tile several chunks share takes device-wide atomics, which leave
         // the L2 as one request per 64 bytes and instruction (the L2s of the
         // XCDs are not coherent): through LDS a row's 64 floats go out in one
         // instruction, four full requests, where lanes adding their own cells
-        // made eight half-empty ones (A+W chunk 14.2 -> 11.6 ms).
+        // made eight half-empty ones (A+W chunk 14.2 -> 11.6 ms).  The PSF adds half
+        // of each row and half of its conjugate mirror image, whose cells
+        // run backwards (row and column 0 receive nothing, so their images
+        // past the grid are never written; W-projection PSF 298 -> 202 us).
         const int w = 2 * min(kTile, a.nx - tx * kTile);
         for (int s = 0; s < 4; ++s)
             for (int p = 0; p < NPOL; ++p) {
@@ -316,9 +319,17 @@ __global__ __launch_bounds__(256, PO ? 2 : 4) void k_grid_tile32(TileArgs a) {
                 for (int r = 0; r < 2; ++r) {
                     const int y = ty * kTile + band + 2 * s + r;
                     const float v = ((const float *)rows[wv])[64 * r + lane];
+                    float *pol = grid + 2 * (((int64_t)P * NPOL + p) * a.pol_stride);
                     if (v != 0.f && lane < w && y < a.ny)
-                        atomicAdd(grid + 2 * (((int64_t)P * NPOL + p) * a.pol_stride +
-                                              (int64_t)y * a.nx + tx * kTile) + lane, v);
+                        atomicAdd(pol + 2 * ((int64_t)y * a.nx + tx * kTile) + lane,
+                                  PSF ? 0.5f * v : v);
+                    if (PSF) {
+                        const int c = kTile - 1 - (lane >> 1);        // its cell in the row
+                        const float u = ((const float *)rows[wv])[64 * r + 2 * c + (lane & 1)];
+                        if (u != 0.f && 2 * c < w && y < a.ny)
+                            atomicAdd(pol + 2 * ((int64_t)(a.ny - y) * a.nx + a.nx - tx * kTile - c) +
+                                          (lane & 1), lane & 1 ? -0.5f * u : 0.5f * u);
+                    }
                 }
                 __builtin_amdgcn_wave_barrier();
             }
@@ -340,13 +351,7 @@ __global__ __launch_bounds__(256, PO ? 2 : 4) void k_grid_tile32(TileArgs a) {
             const float vx = acc[s][p / 2][2 * (p & 1)], vy = acc[s][p / 2][2 * (p & 1) + 1];
             const int64_t base = ((int64_t)P * NPOL + p) * a.pol_stride;
             float *q = grid + 2 * (base + (int64_t)y * a.nx + x);
-            if (PSF) {
-                float *m = grid + 2 * (base + (int64_t)(a.ny - y) * a.nx + (a.nx - x));
-                atomicAdd(q, 0.5f * vx);
-                atomicAdd(q + 1, 0.5f * vy);
-                atomicAdd(m, 0.5f * vx);
-                atomicAdd(m + 1, -0.5f * vy);
-            } else if (set) {
+            if (set) {
                 q[0] = vx;
                 q[1] = vy;
             } else {

@@ -75,3 +75,29 @@ def test_sums_that_are_not_finite_stay_in_their_footprint(form, npol, pointing, 
     # the other samples' sums, to the rounding of another order of additions
     assert (a - b)[:, ~inside].abs().max() <= 1e-5 * b.abs().max()
     assert not torch.isfinite(torch.view_as_real(a[:, inside])).all()
+
+
+@pytest.mark.parametrize("form", ["f64", "f32", "f16cf"])
+@pytest.mark.parametrize("npol", [1, 4])
+@pytest.mark.parametrize("terms,h_max,n_time,pointing", [(TERM_PS | TERM_W, 9, 40, False),
+                                                         (TERM_PS | TERM_W | TERM_A, 17, 12, True),
+                                                         (TERM_PS, 2, 300, False)])
+def test_psf_and_its_mirror_image(form, npol, terms, h_max, n_time, pointing):
+    """Tiles at the grid's first and last rows and columns, whose mirror
+    images cross it, on sides that are and are not whole tiles."""
+    prec = lr.PRECISIONS[form]
+    for nx, ny in ((118, 90), (64, 96)):
+        wl = synth.tiny_workload(n_ant=7, n_time=n_time, nchan=2, npol=npol, nx=nx, ny=ny,
+                                 cell_arcsec=4.0, diameter_m=6000.0, oversample=6,
+                                 n_w=1 if terms == TERM_PS else 4, h_min=2, h_max=h_max,
+                                 terms=terms, fg_hz=[3e9],
+                                 pointing_sigma=3e-5 if pointing else 0.0, cfg_id=281)
+        cf = W.build_cf(wl, prec)
+        v = W.device_vis(wl, prec)
+        ocf = oracle.build_cf(wl.grid, wl.cf)
+        ref, _, _ = Problem.from_workload(wl, ocf, psf=True).psf(wl.weight)
+        g = W.empty_grid(wl, prec)
+        lr.lr_make_psf(cf, v, prec, g)
+        got = g.cpu().numpy()
+        tol = {"f64": 1e-12, **TOL}[form]
+        assert np.linalg.norm(got - ref) <= tol * np.linalg.norm(ref)
