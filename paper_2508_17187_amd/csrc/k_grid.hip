@@ -60,6 +60,8 @@ __device__ __forceinline__ void add_totals(int kept, int flagged, int dropped, d
     __shared__ int cnt[4][3];
     __shared__ double sums[4][NPOL];
     __shared__ int planes[4];
+    // no totals asked for: no wavefront waits for its workgroup's others
+    if (!sumwt && !counters) return;
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     if (counters) {
         for (int off = 32; off > 0; off >>= 1) {

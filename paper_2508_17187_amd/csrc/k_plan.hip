@@ -480,7 +480,15 @@ __global__ void k_tile_ranges(const uint32_t *keys, int64_t n, int64_t n_tiles,
 // 2048^2, above it, parts would cost more in atomic flushes than they
 // balance, 108 -> 118 us) and lower by the number of taps a lane holds, since
 // wider supports keep a SIMD busy with fewer wavefronts (support 15: 800 ->
-// 585 us on 512^2, but 975 -> 1081 us on 1024^2).  Keys sort the tiles by pair count, most first
+// 585 us on 512^2, but 975 -> 1081 us on 1024^2).  The nearer to the line,
+// the fuller the chip is without cuts and the more each cut costs (its tile
+// is cleared first and flushed by atomics): a part is the share of one of
+// kSepFill with few tiles in use and 1 + kSepEven shares at the line, so that
+// only tiles well above the mean are cut there.  Calls with the shares as
+// they are and with longer parts, 80,000 groups on 2048^2: about 900 tiles,
+// kernel 56 -> 44 us (uncut 44); 100 tiles 111 -> 104 us; 10 tiles 96 -> 95 us
+// (uncut 410); on 1024^2, 500 tiles 100 -> 92 us (uncut 261).
+// Keys sort the tiles by pair count, most first
 // (counts of 65535 and more alike: such tiles are cut into equal parts).
 __global__ void k_sep_count(const int32_t *tile_tp, int64_t n_tiles, uint32_t *key,
                             int32_t *tile) {
@@ -495,8 +503,12 @@ __global__ void k_sep_nparts(const int32_t *tile_tp, const int32_t *tile, const 
     int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n_tiles) return;
     int32_t most = kSepPart;
-    if ((int)sums[n_tiles - 1].used < few)
-        most = max(kSepPartMin, min(kSepPart, (tile_tp[n_tiles] + kSepFill - 1) / kSepFill));
+    const int32_t used = (int32_t)sums[n_tiles - 1].used;
+    if (used < few) {
+        const int64_t per = (tile_tp[n_tiles] + kSepFill - 1) / kSepFill;
+        most = (int32_t)max((int64_t)kSepPartMin,
+                            min((int64_t)kSepPart, per + kSepEven * per * used / few));
+    }
     const int32_t t = tile[i];
     const int32_t n = tile_tp[t + 1] - tile_tp[t];
     nparts[i] = (n + most - 1) / most;

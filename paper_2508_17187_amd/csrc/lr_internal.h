@@ -43,6 +43,7 @@ constexpr int32_t kBlockBits = 4;   // blocks of 16 x 16 pixels in the group ord
 constexpr int kSepPart = 4096;     // most (tile, group) pairs per workgroup of the separable gridder
 constexpr int kSepPartMin = 64;    // shortest part when few tiles hold all pairs
 constexpr int kSepFill = 1024;     // parts that fill the chip
+constexpr int kSepEven = 4;        // parts grow to 1 + this many times their share with the tiles in use
 
 // ---------------------------------------------------------------------------
 // Per-channel constants formed on the host in FP64 (no contraction).
