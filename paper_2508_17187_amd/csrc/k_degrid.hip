@@ -354,7 +354,7 @@ __global__ __launch_bounds__(256) void k_degrid_small(DegridArgs a) {
 // width, so a 7 x 7 footprint takes 5 loads of 32 lanes where k_degrid_small
 // needs 20 of 16.  Two groups per half wavefront are in flight.  A group is
 // known from its pixel and offsets alone (geo, one scalar load of four groups
-// instead of four 88-byte records through the vector path).
+// instead of four 80-byte records through the vector path).
 // 6.2 M groups of one sample (8192^2 x 4): degrid call 1379 -> 851 us, of which
 // 140 us expand the groups; supports of 11 and 15: 2413 -> 1759, 4156 -> 2346 us.
 constexpr int kSepGroups = 2;            // groups per half wavefront
