@@ -580,43 +580,22 @@ __global__ __launch_bounds__(256) void k_grid_tile(TileArgs a) {
     T *grid = (T *)a.grid;
     const bool set = excl && a.set;
     if (!excl) {
-        // A tile several chunks share takes device-wide atomics, which leave
-        // the L2 as one request per 64 bytes and instruction: through LDS a
-        // row's 64 values go out in one instruction, eight full requests,
-        // where lanes adding their own cells made sixteen half-empty ones.  The
-        // PSF adds half of each row and half of its conjugate mirror image,
-        // whose cells run backwards (row and column 0 receive nothing, so
-        // their images past the grid are never written; W-projection PSF 507 ->
-        // 346 us).
-        const int wv = threadIdx.x >> 6, w = 2 * min(kTile, a.nx - tx * kTile);
+        const int wv = threadIdx.x >> 6;
+        const TileFlush<T, PSF> flush(grid + 2 * ((int64_t)P * NPOL * a.pol_stride), tx * kTile,
+                                      band0, a.nx, a.ny, a.pol_stride);
         for (int j = 0; j < 4; ++j)
             for (int p = 0; p < NPOL; ++p) {
                 rows[wv][lane] = acc[j][p];
                 __builtin_amdgcn_wave_barrier();
-                for (int r = 0; r < 2; ++r) {
-                    const int y = band0 + 4 * r + j;
-                    const T v = ((const T *)rows[wv])[64 * r + lane];
-                    T *pol = grid + 2 * (((int64_t)P * NPOL + p) * a.pol_stride);
-                    if (v != (T)0 && lane < w && y < a.ny)
-                        atomicAdd(pol + 2 * ((int64_t)y * a.nx + tx * kTile) + lane,
-                                  PSF ? (T)0.5 * v : v);
-                    if (PSF) {
-                        const int c = kTile - 1 - (lane >> 1);        // its cell in the row
-                        const T u = ((const T *)rows[wv])[64 * r + 2 * c + (lane & 1)];
-                        if (u != (T)0 && 2 * c < w && y < a.ny)
-                            atomicAdd(pol + 2 * ((int64_t)(a.ny - y) * a.nx + a.nx - tx * kTile - c) +
-                                          (lane & 1), lane & 1 ? -(T)0.5 * u : (T)0.5 * u);
-                    }
-                }
+                for (int r = 0; r < 2; ++r) flush.add((const T *)rows[wv] + 64 * r, 4 * r + j, p);
                 __builtin_amdgcn_wave_barrier();
             }
         return;
     }
     for (int j = 0; j < 4; ++j) {
         const int y = yb + j;
-        if (set) {
-            if (x >= a.nx || y >= a.ny) continue;
-        } else {
+        if (x >= a.nx || y >= a.ny) continue;
+        if (!set) {
             // cells that received nothing are left alone (adding an exact
             // zero would not change them)
             bool any = false;

@@ -25,7 +25,8 @@
 // own S x S sub-kernel, and a lane outside its columns asks past the end
 // (reading nothing, returning 0; rows outside fall off either end by
 // themselves).  Infinities and NaN would spread through those zeros (0 x inf),
-// so groups whose sums are not finite are added tap by tap afterwards.
+// so groups whose sums or pointing phasors are not finite are added tap by tap
+// afterwards.
 //
 // The loads of the next kBatch groups are in flight while a batch is added.
 #include "k_tile.h"
@@ -127,7 +128,9 @@ __global__ __launch_bounds__(256, PO ? 2 : 4) void k_grid_tile32(TileArgs a) {
                     if (negated(a.cf, gm.form)) v[p] = {-v[p].x, -v[p].y};
                 }
             }
-            bool finite = true;
+            // slopes small enough that the phase overflows nowhere in the tile
+            // (|t O - o| < 2^15), and a loss factor that is a number
+            bool finite = !PO || (fabs(gm.bu) + fabs(gm.bv) < 1e300 && isfinite(gm.f));
             for (int p = 0; p < NPOL; ++p) {
                 v[p].x *= sc;
                 v[p].y *= sc;
@@ -148,7 +151,7 @@ __global__ __launch_bounds__(256, PO ? 2 : 4) void k_grid_tile32(TileArgs a) {
         // the items whose footprints meet this wavefront's band, in order
         uint16_t *list = lists[wv];
         int hits = 0;
-        bool odd = false;              // this lane saw one with a sum that is not finite
+        bool odd = false;              // this lane saw one that is not finite
         for (int w = 0; w < n; w += 64) {
             const int i = w + lane;
             bool hit = false;
@@ -303,34 +306,13 @@ __global__ __launch_bounds__(256, PO ? 2 : 4) void k_grid_tile32(TileArgs a) {
     float *grid = (float *)a.grid;
     const bool set = excl && a.set;
     if (!excl) {
-        // A tile several chunks share takes device-wide atomics, which leave
-        // the L2 as one request per 64 bytes and instruction (the L2s of the
-        // XCDs are not coherent): through LDS a row's 64 floats go out in one
-        // instruction, four full requests, where lanes adding their own cells
-        // made eight half-empty ones (A+W chunk 14.2 -> 11.6 ms).  The PSF adds half
-        // of each row and half of its conjugate mirror image, whose cells
-        // run backwards (row and column 0 receive nothing, so their images
-        // past the grid are never written; W-projection PSF 298 -> 202 us).
-        const int w = 2 * min(kTile, a.nx - tx * kTile);
+        const TileFlush<float, PSF> flush(grid + 2 * ((int64_t)P * NPOL * a.pol_stride), tx * kTile,
+                                          ty * kTile + band, a.nx, a.ny, a.pol_stride);
         for (int s = 0; s < 4; ++s)
             for (int p = 0; p < NPOL; ++p) {
                 rows[wv][lane] = {acc[s][p / 2][2 * (p & 1)], acc[s][p / 2][2 * (p & 1) + 1]};
                 __builtin_amdgcn_wave_barrier();
-                for (int r = 0; r < 2; ++r) {
-                    const int y = ty * kTile + band + 2 * s + r;
-                    const float v = ((const float *)rows[wv])[64 * r + lane];
-                    float *pol = grid + 2 * (((int64_t)P * NPOL + p) * a.pol_stride);
-                    if (v != 0.f && lane < w && y < a.ny)
-                        atomicAdd(pol + 2 * ((int64_t)y * a.nx + tx * kTile) + lane,
-                                  PSF ? 0.5f * v : v);
-                    if (PSF) {
-                        const int c = kTile - 1 - (lane >> 1);        // its cell in the row
-                        const float u = ((const float *)rows[wv])[64 * r + 2 * c + (lane & 1)];
-                        if (u != 0.f && 2 * c < w && y < a.ny)
-                            atomicAdd(pol + 2 * ((int64_t)(a.ny - y) * a.nx + a.nx - tx * kTile - c) +
-                                          (lane & 1), lane & 1 ? -0.5f * u : 0.5f * u);
-                    }
-                }
+                for (int r = 0; r < 2; ++r) flush.add((const float *)rows[wv] + 64 * r, 2 * s + r, p);
                 __builtin_amdgcn_wave_barrier();
             }
         return;
@@ -338,9 +320,8 @@ __global__ __launch_bounds__(256, PO ? 2 : 4) void k_grid_tile32(TileArgs a) {
     const int x = tx * kTile + lx;
     for (int s = 0; s < 4; ++s) {
         const int y = ty * kTile + band + 2 * s + ly;
-        if (set) {
-            if (x >= a.nx || y >= a.ny) continue;
-        } else {
+        if (x >= a.nx || y >= a.ny) continue;
+        if (!set) {
             // cells that received nothing are left alone (adding an exact
             // zero would not change them)
             bool any = false;

@@ -101,3 +101,45 @@ def test_psf_and_its_mirror_image(form, npol, terms, h_max, n_time, pointing):
         got = g.cpu().numpy()
         tol = {"f64": 1e-12, **TOL}[form]
         assert np.linalg.norm(got - ref) <= tol * np.linalg.norm(ref)
+
+
+@pytest.mark.parametrize("form", ["f64"] + list(TOL))
+@pytest.mark.parametrize("call", ["grid", "psf"])
+@pytest.mark.parametrize("bad", [float("nan"), float("inf"), 3e304])
+def test_offsets_that_are_not_finite_stay_in_their_footprint(form, call, bad):
+    """One row whose antenna has such a pointing offset (3e304: the phase
+    overflows a little way outside the footprint, not inside), at the lowest
+    row and column in use: every cell outside its footprints (and, for the
+    PSF, their mirror images) is what the other samples make it, and nothing
+    past the grid is written."""
+    prec = lr.PRECISIONS[form]
+    wl = make(4, 9, 20, True)
+    cf = W.build_cf(wl, prec)
+    v = W.device_vis(wl, prec)
+    psf = call == "psf"
+    m = lr.lr_debug_map(cf, v, psf=psf).cpu().numpy().reshape(-1, 2, 8)
+    h = np.asarray(oracle.build_cf(wl.grid, wl.cf).h)[m[:, :, 4]]
+    low = np.where(m[:, :, 6].all(1), m[:, 0, :2].sum(1) - 2 * h[:, 0], 1 << 30)
+    row = int(low.argmin())
+    a2 = v.ant2.clone()
+    a2[row] = v.ant_dlm.shape[0]
+    dlm = torch.cat([v.ant_dlm, torch.tensor([[bad, bad]], dtype=torch.float64, device="cuda")])
+    ny, nx = wl.grid.ny, wl.grid.nx
+    size = wl.grid.npol * ny * nx
+    buf = torch.zeros(size + 2 * nx, dtype=v.vis.dtype, device="cuda")
+    got = buf[:size].reshape(1, wl.grid.npol, ny, nx)
+    ref = torch.zeros_like(got)
+    fn = lr.lr_make_psf if psf else lr.lr_grid
+    fn(cf, v.with_(ant2=a2, ant_dlm=dlm), prec, got)
+    wt = v.weight.clone()
+    wt[row] = 0
+    fn(cf, v.with_(weight=wt), prec, ref)
+    inside = torch.zeros((ny, nx), dtype=torch.bool, device="cuda")
+    for (pu, pv), k in zip(m[row, :, :2], h[row]):
+        inside[pv - k:pv + k + 1, pu - k:pu + k + 1] = True
+    if psf:
+        inside |= torch.roll(inside.flip((0, 1)), (1, 1), (0, 1))
+    assert not buf[size:].any()
+    # the other samples' sums, to the rounding of another order of additions
+    assert (got - ref)[0][:, ~inside].abs().max() <= 1e-5 * ref.abs().max()
+    assert bad == 3e304 or not torch.isfinite(torch.view_as_real(got[0][:, inside])).all()
