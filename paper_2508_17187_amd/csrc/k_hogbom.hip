@@ -6,9 +6,10 @@
 // of them for itself), subtracts gain x peak x PSF (its centre (ny/2, nx/2) on
 // the peak) from the residual, adds gain x peak to the model, and leaves its
 // own candidates for the next launch in the same pass.  Launch 0 only
-// searches.  Once a launch meets the exit test it sets the stop flag, and later
+// searches.  The launch that meets the exit test records its number, and later
 // launches return at once, so a caller may enqueue the whole budget without
-// waiting.  Ties go to the lowest index.
+// waiting.  (Its own wavefronts may read the number before or after it is
+// written, and go the same way either way.)  Ties go to the lowest index.
 //
 // What bounds it: the image and the PSF read and the image written once per
 // iteration, which the XCDs' L2s do not keep from launch to launch.  No
@@ -24,8 +25,9 @@ namespace lr {
 
 struct HogbomState {
     int32_t iter;         // subtractions done
-    int32_t stop;
+    int32_t stop;         // the launch that met the exit test (kNoStop: none)
 };
+constexpr int32_t kNoStop = 0x7fffffff;
 
 // A candidate peak: signed value and row-major index (-1: none).
 struct Cand {
@@ -76,7 +78,7 @@ __global__ __launch_bounds__(kHogbomThreads) void k_hogbom(T *__restrict__ res,
     T c = (T)0;
     int py = 0, px = 0;
     if (sub) {
-        if (st->stop) return;
+        if (st->stop < k) return;
         Cand g{0.0, -1};
         for (int b = threadIdx.x; b < (int)gridDim.x; b += kHogbomThreads) {
             const Cand p = in[b];
@@ -84,7 +86,7 @@ __global__ __launch_bounds__(kHogbomThreads) void k_hogbom(T *__restrict__ res,
         }
         g = block_best(g);
         if (g.i < 0 || fabs(g.v) < threshold || k > niter) {
-            if (blockIdx.x == 0 && threadIdx.x == 0) st->stop = 1;
+            if (blockIdx.x == 0 && threadIdx.x == 0) st->stop = k;
             return;
         }
         // the scale is rounded to T before use, in the precision of the image
@@ -147,7 +149,7 @@ __global__ __launch_bounds__(kHogbomThreads) void k_hogbom(T *__restrict__ res,
 __global__ void k_hogbom_reset(HogbomState *st) {
     if (threadIdx.x == 0) {
         st->iter = 0;
-        st->stop = 0;
+        st->stop = kNoStop;
     }
 }
 

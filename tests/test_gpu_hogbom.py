@@ -132,3 +132,22 @@ def test_no_finite_pixel_and_reuse_of_the_workspace():
     res[7, 9] = 1.0
     assert lr.lr_hogbom(psf, res, model, 0.1, 0.5, 3, work=work) == 3
     assert model.count_nonzero() == 1 and model[7, 9] != 0
+
+
+@pytest.mark.parametrize("ny,nx", [(30, 40), (700, 1001)])
+def test_exit_long_before_the_budget(ny, nx):
+    """The exit test met after 0 to a few launches of 300, on one and on many
+    workgroups: no workgroup of that launch or of a later one subtracts
+    anything, whatever values the launches before left in its LDS."""
+    rng = np.random.default_rng(ny)
+    psf = rng.normal(0, 0.01, (ny, nx))
+    psf[ny // 2, nx // 2] = 1.0
+    dirty = rng.uniform(-0.01, 0.01, (ny, nx))
+    for k in range(6):
+        dirty[5 * k + 2, 6 * k + 3] = 10.0 * (6 - k)
+    for rep in range(8):
+        for thr in (70.0, 55.0, 35.0, 15.0):
+            m_ref, r_ref, it_ref = hogbom(dirty, psf, 0.9, thr, 300)
+            m, r, it = run(dirty, psf, torch.float64, 0.9, thr, 300)
+            assert it == it_ref < 20
+            assert np.array_equal(m, m_ref) and np.array_equal(r, r_ref)
