@@ -29,7 +29,9 @@ struct HogbomState {
 };
 constexpr int32_t kNoStop = 0x7fffffff;
 
-// A candidate peak: signed value and row-major index (-1: none).
+// A candidate peak: signed value and pixel, y << 32 | x (-1: none).  An image may
+// have more than 2^32 pixels; ordered like the row-major index, and taken apart
+// without a division in every thread.
 struct Cand {
     double v;
     int64_t i;
@@ -91,10 +93,10 @@ __global__ __launch_bounds__(kHogbomThreads) void k_hogbom(T *__restrict__ res,
         }
         // the scale is rounded to T before use, in the precision of the image
         c = (T)(gain * g.v);
-        py = (int)((uint32_t)g.i / (uint32_t)nx);
-        px = (int)((uint32_t)g.i - (uint32_t)py * (uint32_t)nx);
+        py = (int)(g.i >> 32);
+        px = (int)(uint32_t)g.i;
         if (blockIdx.x == 0 && threadIdx.x == 0) {
-            model[g.i] += c;
+            model[(int64_t)py * nx + px] += c;
             st->iter = k;
         }
     }
@@ -106,7 +108,7 @@ __global__ __launch_bounds__(kHogbomThreads) void k_hogbom(T *__restrict__ res,
     uint32_t y = first / nq, q = first - y * nq;
     Cand best{0.0, -1};
     T bv = (T)0;
-    // i increases along the walk: the first of equal pixels wins
+    // pixels come in order along the walk: the first of equal ones wins
     auto see = [&](T r, int64_t i) {
         const T a = r < (T)0 ? -r : r;
         if (a > bv || (best.i < 0 && a == bv)) {
@@ -121,16 +123,16 @@ __global__ __launch_bounds__(kHogbomThreads) void k_hogbom(T *__restrict__ res,
             if (++y >= (uint32_t)ny) break;
         }
         const int x = (int)(4 * q), sy = (int)y - py + cy, sx = x - px + cx;
-        const int64_t i = (int64_t)y * nx + x;
+        const int64_t i = (int64_t)y * nx + x, at = (int64_t)y << 32 | (uint32_t)x;
         const bool row = sub && (unsigned)sy < (unsigned)ny;
-        if (x + 4 <= nx && (!row || (sx >= 0 && sx + 4 <= nx) || sx >= nx || sx + 4 <= 0)) {
+        if (x <= nx - 4 && (!row || (sx >= 0 && sx <= nx - 4) || sx >= nx || sx <= -4)) {
             V r = *(const V *)(res + i);
             if (row && sx >= 0 && sx < nx) {
                 const V p = *(const V *)(psf + (int64_t)sy * nx + sx);
                 r = r - c * p;
                 *(V *)(res + i) = r;
             }
-            for (int e = 0; e < 4; ++e) see(r[e], i + e);
+            for (int e = 0; e < 4; ++e) see(r[e], at + e);
         } else {
             for (int e = 0; e < 4 && x + e < nx; ++e) {
                 T r = res[i + e];
@@ -138,7 +140,7 @@ __global__ __launch_bounds__(kHogbomThreads) void k_hogbom(T *__restrict__ res,
                     r = r - c * psf[(int64_t)sy * nx + sx + e];
                     res[i + e] = r;
                 }
-                see(r, i + e);
+                see(r, at + e);
             }
         }
     }

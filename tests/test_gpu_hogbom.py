@@ -151,3 +151,26 @@ def test_exit_long_before_the_budget(ny, nx):
             m, r, it = run(dirty, psf, torch.float64, 0.9, thr, 300)
             assert it == it_ref < 20
             assert np.array_equal(m, m_ref) and np.array_equal(r, r_ref)
+
+
+def test_more_pixels_than_32_bits():
+    """A peak past pixel 2^32 (FP32, 17 GB per image): its PSF is subtracted
+    around it and nowhere else."""
+    ny, nx = 65540, 65536
+    if torch.cuda.mem_get_info()[0] < 60 << 30:
+        pytest.skip("needs 60 GB of device memory")
+    res = torch.zeros((ny, nx), dtype=torch.float32, device=DEV)
+    psf, model = torch.zeros_like(res), torch.zeros_like(res)
+    cy, cx = ny // 2, nx // 2
+    psf[cy, cx] = 1.0
+    psf[cy - 1, cx + 2] = 0.5
+    y, x = 65537, 1234
+    res[y, x] = 4.0
+    assert lr.lr_hogbom(psf, res, model, 0.5, 0.0, 1) == 1
+    want = {(y, x): 2.0, (y - 1, x + 2): -1.0}
+    assert res.count_nonzero() == 2 and model.count_nonzero() == 1
+    assert model[y, x] == 2.0
+    for (i, j), v in want.items():
+        assert res[i, j] == v
+    del res, psf, model
+    torch.cuda.empty_cache()
