@@ -674,7 +674,7 @@ PlanLayout plan_layout(int64_t n_pairs, int32_t nchan, int32_t h_max, int64_t n_
     // transient (the tile sort of the separable gridder's parts needs
     // n_tiles + 1 entries)
     const int64_t nx_ = std::max(std::max(n, ntp), nt + 1);
-    L.keys_a = take(sizeof(uint64_t) * nx_);
+    L.keys_a = take(std::max(sizeof(uint64_t) * nx_, sizeof(TileSums) * nt));   // keys, then tile sums
     L.keys_b = take(sizeof(uint64_t) * nx_);
     L.vals_a = take(sizeof(int32_t) * nx_);
     L.flags = take(sizeof(int32_t) * nx_);

@@ -98,6 +98,37 @@ def test_few_tiles_in_many_parts(h, form):
     assert np.linalg.norm(g.cpu().numpy() - ref) <= tol
 
 
+@pytest.mark.parametrize("nx,n", [(2048, 1100), (4096, 5000), (4096, 7000), (8192, 22000)])
+def test_parts_do_not_depend_on_the_empty_tiles(nx, n):
+    """The same samples around the centre of a large grid and of a 256^2 one
+    with the same cells: four tiles hold them all, and the packed plans
+    differ by their per-tile arrays alone, so both are cut into as many
+    parts; the grids agree (FP64 rounding of another order of additions)."""
+    plans, grids = [], []
+    for side in (256, nx):
+        wl = synth.tiny_workload(n_ant=4, n_time=-(-n // 6), nchan=1, npol=1, nx=side, ny=side,
+                                 cell_arcsec=6.0 * 256 / side, oversample=20, terms=TERM_PS,
+                                 cfg_id=274)
+        rng = np.random.default_rng(n)
+        wl.obs.uvw[:] = 0.0
+        wl.obs.uvw[:, :2] = rng.uniform(-28, 28, (wl.obs.nrow, 2)) / \
+            (side * wl.grid.cell_l) * C_LIGHT / wl.obs.freq_hz[0]
+        cf = W.build_cf(wl, lr.LR_F64)
+        v = W.device_vis(wl, lr.LR_F64)
+        plan = lr.Plan(cf, v)
+        assert plan.info()["n_kept"] == wl.obs.nrow
+        plans.append(plan.packed().buf.numel())
+        g = W.empty_grid(wl, lr.LR_F64)
+        lr.lr_grid(cf, v.with_(plan=plan), lr.LR_F64, g)
+        lo = side // 2 - 128
+        grids.append(g[..., lo:lo + 256, lo:lo + 256])
+    aligned = lambda words: -(-4 * words // 256) * 256                  # noqa: E731
+    tiles = [(side // 32) ** 2 for side in (256, nx)]
+    per_tile = [aligned(t) + aligned(t + 1) for t in tiles]
+    assert plans[1] - plans[0] == per_tile[1] - per_tile[0]
+    assert (grids[1] - grids[0]).abs().max() <= 1e-12 * grids[0].abs().max()
+
+
 def test_no_pair_kept():
     wl = lattice(6)
     wl.obs.uvw[:, 0] = 1e6
