@@ -350,13 +350,17 @@ __global__ __launch_bounds__(256) void k_degrid_small(DegridArgs a) {
 // grids: 32 lanes per group, lanes over pairs of neighbouring taps (4 pairs x 8
 // rows for supports up to 7, else 8 x 4), starting at even grid columns as in
 // k_degrid_pair, so one 16-byte load brings two cells of a pol and one the two
-// kernel values.  A vector load costs a quarter clock per lane whatever its
-// width, so a 7 x 7 footprint takes 5 loads of 32 lanes where k_degrid_small
-// needs 20 of 16.  Two groups per half wavefront are in flight.  A group is
-// known from its pixel and offsets alone (geo, one scalar load of four groups
-// instead of four 80-byte records through the vector path).
-// 6.2 M groups of one sample (8192^2 x 4): degrid call 1379 -> 851 us, of which
-// 140 us expand the groups; supports of 11 and 15: 2413 -> 1759, 4156 -> 2346 us.
+// kernel values.  A pair that would reach past the row's end moves one column
+// in, so that no cell outside the footprint is read: it may hold anything, and
+// 0 times an infinity is not 0.  A vector load costs a quarter clock per lane
+// whatever its width, so a 7 x 7 footprint takes 5 loads of 32 lanes where
+// k_degrid_small needs 20 of 16.  Two groups per half wavefront are in flight.  A
+// group is known from its pixel and offsets alone (geo, one scalar load of four
+// groups instead of four 80-byte records through the vector path).
+// 6.2 M groups of one sample (8192^2 x 4), degrid call against k_degrid_small:
+// 1352 -> 798 us, of which 140 us expand the groups; supports of 11 and 15:
+// 2304 -> 1668 and 4004 -> 2379 us.  (With pairs that reach past the row's end
+// 846, 1738 and 2322 us.)
 constexpr int kSepGroups = 2;            // groups per half wavefront
 
 struct DegridSepArgs {
@@ -413,31 +417,39 @@ __global__ __launch_bounds__(256) void k_degrid_sep(DegridSepArgs a) {
     const int row = a.nx * 8;
     const char *gbp[NPOL];
     for (int p = 0; p < NPOL; ++p) gbp[p] = (const char *)a.grid + uni64(p * a.pol_stride * 8);
-    // the kernel element before a group's sub-kernel and its walk, the grid
-    // byte of its pair (0, 0), per group of this lane's half
+    // of this lane's half, per group: kernel element and grid byte of this lane's
+    // pair in row 0, the kernel's walk, and which cells of the pair count
     uint32_t kb[NG], gb[NG];
-    int su[NG], sv[NG], lead[NG];
+    int sv[NG];
+    bool fu[NG], in0[NG], in1[NG];
     for (int u = 0; u < NG; ++u) {
         uint32_t kk[2], gg[2];
-        int uu[2], vv[2], ll[2];
+        int vv[2];
+        bool ff[2], ll[2];
         for (int q = 0; q < 2; ++q) {
             const int64_t g = gw + 2 * u + q;
             const int64_t geo = a.geo[g < a.n_groups ? g : a.n_groups - 1];
             const int pu = (int)(geo & 0xFFFF), pv = (int)((geo >> 16) & 0xFFFF);
             const int ou = (int)(int16_t)(geo >> 32), ov = (int)(int16_t)(geo >> 48);
-            const bool fu = ou > 0, fv = ov > 0;
-            const int cell0 = ((half - abs(ov)) * no + (half - abs(ou))) * S * S;
-            ll[q] = (pu - h) & 1;
-            uu[q] = fu ? -2 : 2;
+            const bool fv = ov > 0;
+            ff[q] = ou > 0;
+            ll[q] = ((pu - h) & 1) != 0;
             vv[q] = fv ? -S : S;
-            kk[q] = (uint32_t)(cell0 + (fu ? S - 2 + ll[q] : -ll[q]) + (fv ? (S - 1) * S : 0));
-            gg[q] = (uint32_t)((int64_t)(pv - h) * row + (pu - h - ll[q]) * 8);
+            // the first row's pair (0, 1), where a flipped row holds it last
+            kk[q] = (uint32_t)(((half - abs(ov)) * no + (half - abs(ou))) * S * S +
+                               (ff[q] ? S - 2 : 0) + (fv ? (S - 1) * S : 0));
+            gg[q] = (uint32_t)((int64_t)(pv - h) * row + (pu - h) * 8);
         }
-        kb[u] = second ? kk[1] : kk[0];
-        gb[u] = second ? gg[1] : gg[0];
-        su[u] = second ? uu[1] : uu[0];
+        fu[u] = second ? ff[1] : ff[0];
         sv[u] = second ? vv[1] : vv[0];
-        lead[u] = second ? ll[1] : ll[0];
+        // the aligned pair (t, t + 1); one that reaches past the row's end is
+        // read one column further in, where its other cell is another lane's
+        const int t = 2 * c - ((second ? ll[1] : ll[0]) ? 1 : 0);
+        const int at = min(max(t, 0), S - 2);
+        in0[u] = t <= S - 2;
+        in1[u] = t >= 0 && t < S;
+        kb[u] = (second ? kk[1] : kk[0]) + (uint32_t)(fu[u] ? -at : at);
+        gb[u] = (second ? gg[1] : gg[0]) + (uint32_t)(at * 8);
     }
     const float sc = E == 4 ? a.sc[0] : 1.0f;
     float sum[NG][NV];
@@ -445,18 +457,16 @@ __global__ __launch_bounds__(256) void k_degrid_sep(DegridSepArgs a) {
         for (int i = 0; i < NV; ++i) sum[u][i] = 0.f;
     for (int r0 = 0; r0 < S; r0 += NR) {
         const int r = r0 + rl;
+        const bool ok = r < S;
+        const int rr = ok ? r : 0;             // lanes past the footprint add nothing
         Raw2 kv[NG];
         f32x4_a8 gv[NG][NPOL];
         for (int u = 0; u < NG; ++u) {
-            // lanes past the footprint take pair (0, 1) (in bounds) and add nothing
-            const bool ok = r < S && 2 * c - lead[u] < S;
-            const int rr = ok ? r : 0, cc = ok ? c : 1;
-            kv[u] = *(const Raw2 *)((const char *)a.table + (int64_t)(int32_t)(kb[u] + rr * sv[u] + cc * su[u]) * E);
-            const uint32_t at = gb[u] + (uint32_t)(rr * row + cc * 16);
+            kv[u] = *(const Raw2 *)((const char *)a.table + (int64_t)(int32_t)(kb[u] + rr * sv[u]) * E);
+            const uint32_t at = gb[u] + (uint32_t)(rr * row);
             for (int p = 0; p < NPOL; ++p) gv[u][p] = *(const f32x4_a8 *)(gbp[p] + at);
         }
         for (int u = 0; u < NG; ++u) {
-            const int t = 2 * c - lead[u];
             float c0, c1;
             if constexpr (E == 8) {
                 c0 = kv[u].x;
@@ -465,13 +475,13 @@ __global__ __launch_bounds__(256) void k_degrid_sep(DegridSepArgs a) {
                 c0 = CFReal<ST>::decode((uint16_t)(kv[u].x & 0xFFFF), sc);
                 c1 = CFReal<ST>::decode((uint16_t)(kv[u].y & 0xFFFF), sc);
             }
-            if (su[u] < 0) {
+            if (fu[u]) {
                 const float s = c0;
                 c0 = c1;
                 c1 = s;
             }
-            if (r >= S || t < 0 || t >= S) c0 = 0.f;
-            if (r >= S || t + 1 >= S) c1 = 0.f;
+            if (!ok || !in0[u]) c0 = 0.f;
+            if (!ok || !in1[u]) c1 = 0.f;
             for (int p = 0; p < NPOL; ++p) {
                 sum[u][2 * p] = fmaf(c1, gv[u][p].z, fmaf(c0, gv[u][p].x, sum[u][2 * p]));
                 sum[u][2 * p + 1] = fmaf(c1, gv[u][p].w, fmaf(c0, gv[u][p].y, sum[u][2 * p + 1]));

@@ -65,3 +65,42 @@ def test_group_counts(n_time):
 def test_other_kernels(form, nplane):
     got, ref = degrid(form, 3, 4, 40, nplane)
     assert np.linalg.norm(got - ref) <= TOL[form] * np.linalg.norm(ref)
+
+
+@pytest.mark.parametrize("form", ["f64", "f32", "f16cf", "bf16cf"])
+@pytest.mark.parametrize("npol", [1, 4])
+@pytest.mark.parametrize("h", [1, 2, 3, 4, 7])
+@pytest.mark.parametrize("bad", [float("inf"), float("nan")])
+def test_cells_outside_a_footprint_are_not_read_into_it(form, npol, h, bad):
+    """Every cell but one footprint's holds a value that is not finite: the
+    footprint's sample is what zeros there give, bit for bit, whether it
+    begins at an odd or an even column, mirrored or not."""
+    prec = lr.PRECISIONS[form]
+    wl = synth.tiny_workload(n_ant=6, n_time=30, nchan=1, npol=npol, nx=74, ny=60,
+                             cell_arcsec=6.0, diameter_m=3500.0, oversample=10, terms=TERM_PS,
+                             h_min=h, h_max=h, cfg_id=291)
+    rng = np.random.default_rng(291 + h)
+    wl.obs.uvw[:, :2] += rng.normal(0.0, 30.0, wl.obs.uvw[:, :2].shape)
+    cf = W.build_cf(wl, prec)
+    v = W.device_vis(wl, prec)
+    v.plan = lr.Plan(cf, v)
+    v.weight.fill_(1.0)
+    m = lr.lr_debug_map(cf, v).cpu().numpy()[:, 0]
+    shape = (1, npol, 60, 74)
+    g = rng.standard_normal(shape) + 1j * rng.standard_normal(shape)
+    g = torch.as_tensor(g, device="cuda").to(v.vis.dtype)
+    for odd in (0, 1):
+        for side in (-1, 1):
+            rows = np.nonzero((m[:, 6] == 1) & ((m[:, 0] - h) % 2 == odd) &
+                              (np.where(m[:, 2] > 0, 1, -1) == side))[0]
+            for row in rows[:3]:
+                pu, pv = m[row, :2]
+                out = []
+                for fill in (0.0, bad):
+                    q = torch.full_like(g, complex(fill, fill))
+                    cut = np.s_[..., pv - h:pv + h + 1, pu - h:pu + h + 1]
+                    q[cut] = g[cut]
+                    lr.lr_degrid(cf, v, prec, q)
+                    out.append(v.vis[row, 0].cpu().numpy().copy())
+                assert np.isfinite(out[1]).all() and np.array_equal(out[0], out[1])
+            assert len(rows)
