@@ -380,8 +380,8 @@ static void col_shape(int64_t n_pairs, int64_t L, int64_t &ncb, int32_t &n_block
 }
 
 // ---------------------------------------------------------------------------
-// Tile gridder.  One workgroup per chunk of (tile, group) pairs of one
-// 32 x 32 tile; thread t owns the four cells (x0 + t % 32, y0 + 4 (t / 32) + j)
+// Tile gridder of the FP64 form.  One workgroup per chunk of (tile, group)
+// pairs of one 32 x 32 tile; thread t owns the four cells (x0 + t % 32, y0 + 4 (t / 32) + j)
 // and accumulates Ct(o, t) phi(t) A_g for every group whose footprint covers
 // them, in registers.  A chunk that holds all of its tile's pairs writes the
 // tile with plain stores (GRID_SET: every cell; GRID_ADD: read-modify-write
@@ -395,8 +395,6 @@ struct TileItem {
     int64_t cf_off;
     int32_t bx, by;   // footprint origin p - h
     int32_t S, form;
-    float sc;         // 2^-e of the CF plane
-    int32_t h;
 };
 
 // Items a wavefront takes per step: their kernel loads are in flight
@@ -405,11 +403,12 @@ constexpr int kItemBatch = 4;
 // items of a chunk as ballot bits, 64 per word
 constexpr int kMaskWords = (kChunkMax + 63) / 64;
 
-template <typename T, int ST, int NPOL, bool PO, bool PSF, bool RE, bool DET>
+template <int NPOL, bool PO, bool PSF, bool RE, bool DET>
 __global__ __launch_bounds__(256) void k_grid_tile(TileArgs a) {
     constexpr int B = kItemBatch;
-    constexpr int E = CFRaw<ST>::bytes;
-    typedef typename std::conditional<RE, typename CFReal<ST>::R, typename CFRaw<ST>::R>::type Raw;
+    constexpr int E = 16;
+    typedef double T;
+    typedef typename std::conditional<RE, double, double2>::type Raw;
     __shared__ TileItem items[kChunkMax];
     __shared__ cpx<T> avs[kChunkMax * NPOL];
     __shared__ GroupMeta gms[PO ? kChunkMax : 1];
@@ -457,8 +456,6 @@ __global__ __launch_bounds__(256) void k_grid_tile(TileArgs a) {
             ti.by = gm.pv - h;
             ti.S = 2 * h + 1;
             ti.form = gm.form;
-            ti.sc = a.cf.scale[(int64_t)gm.fg * a.cf.n_w + gm.k];
-            ti.h = h;
             items[t] = ti;
             if (a.mix == 0) {
                 for (int p = 0; p < NPOL; ++p) avs[t * NPOL + p] = Av[(int64_t)g * NPOL + p];
@@ -513,7 +510,6 @@ __global__ __launch_bounds__(256) void k_grid_tile(TileArgs a) {
             Raw cv[B][4];
             bool ok[B][4];
             int dxs[B], rs[B];
-            float scs[B];
             // the kernel loads of the whole batch are issued before any is used;
             // an item's fields are wave-uniform, so its sub-kernel base address
             // is scalar and a lane only adds its 32-bit offset; cells outside
@@ -525,7 +521,6 @@ __global__ __launch_bounds__(256) void k_grid_tile(TileArgs a) {
                 const TileItem ti = items[idx[b]];
                 const int S = uni(ti.S);
                 const char *base = table + uni64(ti.cf_off) * E;
-                scs[b] = ti.sc;
                 const int dx = x - uni(ti.bx);
                 const int r = yb - uni(ti.by);
                 dxs[b] = dx;
@@ -553,16 +548,16 @@ __global__ __launch_bounds__(256) void k_grid_tile(TileArgs a) {
                 for (int j = 0; j < 4; ++j) {
                     if (!ok[b][j]) continue;
                     if constexpr (RE) {
-                        const T c = CFReal<ST>::decode(cv[b][j], scs[b]);
+                        const T c = cv[b][j];
                         for (int p = 0; p < NPOL; ++p) {
                             acc[j][p].x = fma(c, av[p].x, acc[j][p].x);
                             acc[j][p].y = fma(c, av[p].y, acc[j][p].y);
                         }
                     } else {
-                        cpx<T> cw = CFRaw<ST>::decode(cv[b][j], scs[b]);
+                        cpx<T> cw = {cv[b][j].x, cv[b][j].y};
                         if (cj) cw.y = -cw.y;
                         if (PO) {
-                            const int h = items[t].h;
+                            const int h = items[t].S >> 1;
                             cw = cmul(cw, phasor<T>(gms[t], dxs[b] - h, rs[b] + j - h, a.cf.O));
                         }
                         for (int p = 0; p < NPOL; ++p) cmac(acc[j][p], cw, av[p]);
@@ -914,36 +909,26 @@ hipError_t launch_counts(const lr_plan *P, const void *weight, int precision, in
     return presum_np<float>(P, v, nullptr, sumwt, counters, false, s);
 }
 
-template <typename T, int ST, int NPOL>
+template <int NPOL>
 static hipError_t grid_t(const TileArgs &ta, int64_t n_blocks, bool po, bool psf, bool det,
                          hipStream_t s) {
     dim3 grd((unsigned)n_blocks), blk(256);
     // the point-spread function's mirror image is always flushed with
     // atomics: it has no deterministic form
     if (po) {
-        if (psf) hipLaunchKernelGGL((k_grid_tile<T, ST, NPOL, true, true, false, false>), grd, blk, 0, s, ta);
-        else if (det) hipLaunchKernelGGL((k_grid_tile<T, ST, NPOL, true, false, false, true>), grd, blk, 0, s, ta);
-        else hipLaunchKernelGGL((k_grid_tile<T, ST, NPOL, true, false, false, false>), grd, blk, 0, s, ta);
+        if (psf) hipLaunchKernelGGL((k_grid_tile<NPOL, true, true, false, false>), grd, blk, 0, s, ta);
+        else if (det) hipLaunchKernelGGL((k_grid_tile<NPOL, true, false, false, true>), grd, blk, 0, s, ta);
+        else hipLaunchKernelGGL((k_grid_tile<NPOL, true, false, false, false>), grd, blk, 0, s, ta);
     } else if (ta.cf.real) {
-        if (psf) hipLaunchKernelGGL((k_grid_tile<T, ST, NPOL, false, true, true, false>), grd, blk, 0, s, ta);
-        else if (det) hipLaunchKernelGGL((k_grid_tile<T, ST, NPOL, false, false, true, true>), grd, blk, 0, s, ta);
-        else hipLaunchKernelGGL((k_grid_tile<T, ST, NPOL, false, false, true, false>), grd, blk, 0, s, ta);
+        if (psf) hipLaunchKernelGGL((k_grid_tile<NPOL, false, true, true, false>), grd, blk, 0, s, ta);
+        else if (det) hipLaunchKernelGGL((k_grid_tile<NPOL, false, false, true, true>), grd, blk, 0, s, ta);
+        else hipLaunchKernelGGL((k_grid_tile<NPOL, false, false, true, false>), grd, blk, 0, s, ta);
     } else {
-        if (psf) hipLaunchKernelGGL((k_grid_tile<T, ST, NPOL, false, true, false, false>), grd, blk, 0, s, ta);
-        else if (det) hipLaunchKernelGGL((k_grid_tile<T, ST, NPOL, false, false, false, true>), grd, blk, 0, s, ta);
-        else hipLaunchKernelGGL((k_grid_tile<T, ST, NPOL, false, false, false, false>), grd, blk, 0, s, ta);
+        if (psf) hipLaunchKernelGGL((k_grid_tile<NPOL, false, true, false, false>), grd, blk, 0, s, ta);
+        else if (det) hipLaunchKernelGGL((k_grid_tile<NPOL, false, false, false, true>), grd, blk, 0, s, ta);
+        else hipLaunchKernelGGL((k_grid_tile<NPOL, false, false, false, false>), grd, blk, 0, s, ta);
     }
     return hipGetLastError();
-}
-
-template <typename T, int ST>
-static hipError_t grid_np(const TileArgs &ta, int64_t n_blocks, int npol, bool po, bool psf,
-                          bool det, hipStream_t s) {
-    switch (npol) {
-        case 1: return grid_t<T, ST, 1>(ta, n_blocks, po, psf, det, s);
-        case 2: return grid_t<T, ST, 2>(ta, n_blocks, po, psf, det, s);
-        default: return grid_t<T, ST, 4>(ta, n_blocks, po, psf, det, s);
-    }
 }
 
 hipError_t launch_grid(const lr_plan *P, const CFView &cf, const void *A, void *grid,
@@ -962,7 +947,13 @@ hipError_t launch_grid(const lr_plan *P, const CFView &cf, const void *A, void *
     bool po = P->po != 0;
     bool psf = mode == GRID_PSF;
     det = det && !psf;
-    if (precision == LR_F64) return grid_np<double, LR_F64>(ta, nc, npol, po, psf, det, s);
+    if (precision == LR_F64) {
+        switch (npol) {
+            case 1: return grid_t<1>(ta, nc, po, psf, det, s);
+            case 2: return grid_t<2>(ta, nc, po, psf, det, s);
+            default: return grid_t<4>(ta, nc, po, psf, det, s);
+        }
+    }
     return launch_grid_tile32(ta, nc, precision, npol, po, psf, det, s);
 }
 

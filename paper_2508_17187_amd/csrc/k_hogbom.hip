@@ -72,8 +72,8 @@ template <typename T>
 __global__ __launch_bounds__(kHogbomThreads) void k_hogbom(T *__restrict__ res,
                                                            const T *__restrict__ psf, T *model,
                                                            int32_t nx, int32_t ny, double gain,
-                                                           double threshold, int32_t niter,
-                                                           int32_t k, HogbomState *st,
+                                                           double threshold, int32_t k,
+                                                           HogbomState *st,
                                                            const Cand *in, Cand *out) {
     typedef typename Quad<T>::V V;
     const bool sub = k > 0;
@@ -87,7 +87,7 @@ __global__ __launch_bounds__(kHogbomThreads) void k_hogbom(T *__restrict__ res,
             if (better(p, g)) g = p;
         }
         g = block_best(g);
-        if (g.i < 0 || fabs(g.v) < threshold || k > niter) {
+        if (g.i < 0 || fabs(g.v) < threshold) {
             if (blockIdx.x == 0 && threadIdx.x == 0) st->stop = k;
             return;
         }
@@ -170,7 +170,7 @@ static hipError_t hogbom_t(T *res, const T *psf, T *model, int32_t nx, int32_t n
         kHogbomBlocks, (quads + kHogbomThreads - 1) / kHogbomThreads);
     for (int32_t k = 0; k <= niter; ++k) {
         hipLaunchKernelGGL(k_hogbom<T>, dim3(blocks), dim3(kHogbomThreads), 0, s, res, psf, model,
-                           nx, ny, gain, threshold, niter, k, st,
+                           nx, ny, gain, threshold, k, st,
                            part + ((k + 1) & 1) * kHogbomBlocks, part + (k & 1) * kHogbomBlocks);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
