@@ -10,8 +10,9 @@ import pytest
 
 import oracle
 import synth
-from oracle.cfbuild import TERM_PS, quantised_table
+from oracle.cfbuild import TERM_A, TERM_PS, quantised_table
 from oracle.native import Problem
+from synth.observation import C_LIGHT
 
 pytestmark = pytest.mark.gpu
 
@@ -65,6 +66,35 @@ def test_group_counts(n_time):
 def test_other_kernels(form, nplane):
     got, ref = degrid(form, 3, 4, 40, nplane)
     assert np.linalg.norm(got - ref) <= TOL[form] * np.linalg.norm(ref)
+
+
+@pytest.mark.parametrize("form", ["f32", "f16cf"])
+@pytest.mark.parametrize("npol", [1, 4])
+@pytest.mark.parametrize("terms", [TERM_PS, TERM_PS | TERM_A])
+@pytest.mark.parametrize("h", [8, 20, 31, 32, 62, 63, 64, 65, 128])
+def test_pairs_per_row_around_a_wavefront(form, npol, terms, h):
+    """Wider supports, real and complex: rows of 9 to 129 pairs on the 64
+    lanes, on both sides of one and of two rows per step.  Against the stored
+    table, at the library's FP32 bound (each lane adds up to 1000 products)."""
+    prec = lr.PRECISIONS[form]
+    wl = synth.tiny_workload(n_ant=4, n_time=40, nchan=1, npol=npol, nx=2 * h + 38, ny=2 * h + 30,
+                             cell_arcsec=6.0, oversample=4, terms=terms, h_min=h, h_max=h,
+                             fg_hz=[3e9], cfg_id=292)
+    rng = np.random.default_rng(292 + h)
+    wl.obs.uvw[:, :2] = rng.uniform(-14, 14, (wl.obs.nrow, 2)) / \
+        ((2 * h + 38) * wl.grid.cell_l) * C_LIGHT / wl.obs.freq_hz[0]
+    shape = (1, npol, 2 * h + 30, 2 * h + 38)
+    g = (rng.standard_normal(shape) + 1j * rng.standard_normal(shape)).astype(np.complex64)
+    cf = W.build_cf(wl, prec)
+    v = W.device_vis(wl, prec)
+    m = lr.lr_debug_map(cf, v).cpu().numpy()[:, 0]
+    # odd and even starts, mirrored and not on each axis
+    assert len({(a % 2, b > 0, c > 0) for a, b, c, k in m[:, [0, 2, 3, 6]] if k}) == 8
+    lr.lr_degrid(cf, v, prec, torch.as_tensor(g, device="cuda"))
+    ocf = oracle.build_cf(wl.grid, wl.cf)
+    pr = Problem.from_workload(wl, ocf, table=quantised_table(ocf, STORE[form]))
+    ref = pr.degrid(g.astype(np.complex128), wl.weight)
+    assert np.linalg.norm(v.vis.cpu().numpy() - ref) <= 1e-5 * np.linalg.norm(ref)
 
 
 @pytest.mark.parametrize("form", ["f64", "f32", "f16cf", "bf16cf"])
