@@ -255,7 +255,7 @@ lr_status lr_plan_info(const lr_plan *plan, int64_t *n_groups, int64_t *n_kept,
  * sums of weights come from fixed per-(channel, row block) partials and
  * fixed trees; each grid tile is written by one workgroup, which takes the
  * tile's chunks in order, instead of atomic flushes of tiles shared by
- * several chunks.  Slower (about 2.2x per gridding call on data whose
+ * several chunks.  Slower (about 5x per gridding call on data whose
  * samples merge into large groups); the results equal the default mode's
  * up to FP rounding order.  The workspace size of LR_OP_GRID and
  * LR_OP_SUMWT always includes what this mode needs.  lr_make_psf keeps its
@@ -322,9 +322,10 @@ lr_status lr_grid_static(const lr_cf *cf, const lr_vis *vis, lr_precision precis
  * weights enter the sum.  counters may be NULL.  With a Mueller table
  * (pol_beam > 0) correlation q sums conj(Ct_qp) over the grid pols p its
  * row of the sparse matrix holds (one pass per kind).  The grid must hold
- * finite values: with FP32 grids the gather reads two cells per load and may
- * take in one cell beyond a footprint row's end with weight 0, so an Inf or
- * NaN there would reach the sample. */
+ * finite values: with FP32 grids and tables that hold a support above 15 the
+ * gather reads two cells per load and may take in one cell beyond a
+ * footprint row's end with weight 0, so an Inf or NaN there would reach the
+ * sample. */
 lr_status lr_degrid(const lr_cf *cf, lr_vis *vis, lr_precision precision, const void *grid,
                     int64_t *counters, void *work, size_t work_bytes, lr_stream stream);
 

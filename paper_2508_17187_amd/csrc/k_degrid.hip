@@ -1,5 +1,5 @@
-// Degridding D (Eq. ME-MOD-GRIDDED): one wavefront (or a quarter of one for
-// supports up to 15) per group gathers sum_t conj(Ct phi) grid over the
+// Degridding D (Eq. ME-MOD-GRIDDED): one wavefront (half or a quarter of one
+// for supports up to 15) per group gathers sum_t conj(Ct phi) grid over the
 // footprint and reduces across lanes.
 #include "k_common.h"
 
@@ -23,9 +23,10 @@ struct DegridArgs {
 // orders the groups of one kernel plane by blocks of 16 x 16 pixels, so a run's
 // footprints share most of their cells and its kernels come from one plane,
 // and both stay in that XCD's L2.  Degridding with runs of 1 / 4 / 16 / 32 / 128:
-// A+W chunk 18.0 / 15.7 / 14.4 / 14.1 / 13.8 ms, W-projection (FP32) 133 / 116 /
-// 113 / 113 / 119 us, a job of 1e4 groups 38.9 / 38.5 / 38.1 / 38.1 / 48.4 us
-// (long runs leave XCDs idle at the end).  The launch is padded to whole rounds.
+// A+W chunk 14.9 / 13.1 / 12.5 / 12.4 / 12.2 ms, W-projection (FP32) 128 / 107 /
+// 104 / 103 / 109 us, a job of 1e4 groups 35.5 / 33.2 / 32.0 / 32.2 / 36.6 us
+// (long runs leave XCDs idle at the end).  The launch is padded to whole rounds
+// (dealing the last, partial round one by one instead: W-projection 103 -> 105 us).
 constexpr int kDegridRun = 32;
 __device__ __forceinline__ int64_t xcd_run(unsigned b) {
     return ((b >> 3) / kDegridRun * 8 + (b & 7)) * kDegridRun + (b >> 3) % kDegridRun;

@@ -94,9 +94,9 @@ hipError_t launch_debug_map(int64_t nrow, int32_t nchan, const double *uvw,
 
 // ---------------------------------------------------------------------------
 // Sort keys.  Fields from most to least significant: plane, A-term group,
-// w-plane, block of pixels (v, u), conj, p_v, p_u in the block, [baseline, channel when a pointing phasor is
-// applied], o_v, o_u.  Keys of dropped or skipped pairs are all ones, which
-// no kept pair's 63 bits reach.
+// w-plane, block of pixels (v, u), conj, p_v, p_u in the block, [baseline,
+// channel when a pointing phasor is applied], o_v, o_u.  Keys of dropped or
+// skipped pairs are all ones, which no kept pair's 63 bits reach.
 constexpr uint64_t kDropKey = ~0ull;
 
 __device__ __forceinline__ void put(unsigned __int128 &key, uint32_t v, int bits) {
@@ -816,13 +816,13 @@ hipError_t build_plan_device(lr_plan *P, char *buf, const PlanLayout &L, const d
         hipLaunchKernelGGL(k_sep_fill, dim3(blocks(nt, 256)), dim3(256), 0, s, P->tile_tp, tile,
                            nparts, first, nt, P->sep_part, P->sep_shared, pc);
     } else {
-        // with a kernel table the last-level cache holds, the gridder launches
-        // chunks largest first (a stable sort: ties keep tile order), so the
-        // long ones do not trail the launch; with a larger table it launches
-        // them plane by plane (tile order within a plane), so the chunks in
-        // flight read one plane of the table, which the cache holds, instead
-        // of all of them.  Sorted at their most possible number, so that the
-        // host need not wait for the count.
+        // with a small kernel table (lpt) the gridder launches chunks largest
+        // first (a stable sort: ties keep tile order), so the long ones do not
+        // trail the launch; with a larger table it launches them plane by
+        // plane (tile order within a plane), so the chunks in flight read one
+        // plane of the table, which the caches hold, instead of all of them.
+        // Sorted at their most possible number, so that the host need not wait
+        // for the count.
         const uint32_t slots = (uint32_t)std::min<int64_t>(ntp, ntp / per + nt);
         int end_bits = kCostBits;
         if (lpt) {

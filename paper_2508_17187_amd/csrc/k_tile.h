@@ -1,5 +1,5 @@
-// Arguments and helpers the tile gridders share (k_grid.hip: FP64,
-// k_tile32.hip: FP32 on the matrix cores).
+// Arguments, chunk order, clearing and shared-tile flush of the tile gridders
+// (k_grid.hip: FP64, k_tile32.hip: FP32 on the matrix cores).
 #pragma once
 
 #include "k_common.h"

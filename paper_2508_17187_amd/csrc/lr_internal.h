@@ -175,8 +175,8 @@ struct lr_plan {
     int32_t *chunk_tile;       // [n_chunks] tile id: (plane * nty + ty) * ntx + tx
     int32_t *chunk_excl;       // [n_chunks] 1 when the chunk holds all pairs of its tile
     int32_t *chunk_order;      // [n_chunks] launch order: by estimated work, largest
-                               // first, for kernel tables the last-level cache holds;
-                               // plane by plane for larger ones (null: no chunks)
+                               // first, for small kernel tables, plane by plane for
+                               // larger ones (null: tile order, for separable tables)
     int32_t by_plane;          // chunk_order goes plane by plane
     int32_t *tile_state;       // [n_tiles] 0 no pairs, 1 one exclusive chunk, 2 several chunks
     int64_t n_tiles;           // nplane * nty * ntx
